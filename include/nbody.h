@@ -26,7 +26,9 @@
  *   pot_i = -G sum_{j != i} m_j / sqrt(|d_ij|^2 + eps_b^2)   (negative for bound systems)
  *   When eps_b > 0 the j = i term is exactly zero and the kernels may include it; when
  *   eps_b = 0 it is excluded explicitly.  The pair sum is evaluated in full (N^2 terms per
- *   cluster, no use of Newton's third law), as the paper does in Sect. 4.2.
+ *   cluster).  Clusters of 4096 to 2^20 particles evaluate each unordered pair once and use it for
+ *   both particles (the pair forces of Eq. 2 are antisymmetric); the others evaluate every ordered
+ *   term, as the paper does in Sect. 4.2.
  *
  * Precision modes (nbody_system.prec)
  *   NB_FP32    pure single precision: pairs, accumulation and state updates in FP32; every state
@@ -130,14 +132,16 @@ int nbody_create(int device, nbody_ctx** out);
 void nbody_destroy(nbody_ctx* ctx);
 
 /* Bytes of device workspace the calls below need for `sys` (0 if `sys` is invalid; then
- * nbody_last_error() says why): 32 bytes per particle, plus 32 bytes per particle and j-range
- * for clusters whose sums are split into several source ranges (a cluster of N particles uses
- * about 2^22/N ranges, a power of two of at most 8 (16 from 2^15 particles on) with at least 128
- * sources each, so clusters of 256..2^21 particles are split; an unsplit cluster in the
- * NB_GALAXY_ALLEN_SANTILLAN field takes one such range too, since a separate pass finishes it),
+ * nbody_last_error() says why): 32 bytes per particle; for clusters of 4096 to 2^20 particles
+ * 24 bytes per particle and segment (segments of 256 particles below 8192, 512 below 65536, 1024
+ * from there), for at most 68 segments at a time and at most 204 MiB per cluster; for the others 32
+ * bytes per particle and j-range where the sums are split into several source ranges (a cluster of N
+ * particles has about 2^22/N ranges, a power of two of at most 8 (16 from 2^15 particles on) with at
+ * least 128 sources each; an unsplit cluster in the
+ * NB_GALAXY_ALLEN_SANTILLAN field takes one such range too, since a separate pass finishes it);
  * plus 48 bytes per particle, 4 KiB per 2048 particles and 4 KiB per cluster for the sort of
- * NB_FP32DL, and for its per-item frames and far-tile bits 32 bytes per
- * 64 particles and range plus N_b^2 / 2^15 bytes per cluster, plus O(B + N/64) bookkeeping.  The
+ * NB_FP32DL, and for its frames and far-tile bits 32 bytes per 256 particles, or in the split clusters
+ * 32 bytes per 64 particles and range plus N_b^2 / 2^15 bytes per cluster, plus O(B + N/64) bookkeeping.  The
  * workspace must be 256-byte aligned;
  * its contents are the library's between calls (the caller must not modify it while calls using
  * it are in flight). */
@@ -161,11 +165,12 @@ int nbody_accel(nbody_ctx* ctx, const nbody_system* sys, const double* pos, cons
  * the library's first use on that GPU until the process ends; the tables go up through a pinned
  * staging buffer of NB_NOALLOC_TABLE_BYTES that nbody_create allocated.  The call itself allocates
  * nothing (no hipMalloc, hipFree or pinned allocation).  Same arguments, results and errors as
- * nbody_accel, and bitwise the same accelerations and potentials.  Limits: a system whose
- * nbody_workspace_bytes exceeds NB_NOALLOC_SCRATCH_BYTES (a single cluster of more than about 8.1
- * million particles, 1.4 million in NB_FP32DL) or whose tables exceed NB_NOALLOC_TABLE_BYTES (more
- * than about 39,000 clusters) returns NB_ERR_ARG; these two checks run first and need
- * neither a context nor a GPU.  Every call on one GPU shares that GPU's scratch, which keeps the
+ * nbody_accel, and bitwise the same accelerations and potentials (clusters of 4096 to 2^20 particles
+ * take fewer segments at a time where the scratch has no room for more).  Limits: a system that with
+ * every cluster split into j-ranges would need more than NB_NOALLOC_SCRATCH_BYTES of workspace (a
+ * single cluster of more than about 8.1 million particles, 1.4 million in NB_FP32DL) or more than
+ * NB_NOALLOC_TABLE_BYTES of tables (more than about 39,000 clusters) returns NB_ERR_ARG; these two
+ * checks run first and need neither a context nor a GPU.  Every call on one GPU shares that GPU's scratch, which keeps the
  * last call's contents (the per-call counters are cleared by the call's own table upload): calls
  * that overlap on one GPU (several streams, threads or contexts at once) race and give wrong
  * results, so order them on one stream.  Asynchronous. */
@@ -235,7 +240,8 @@ const char* nbody_last_error(void);
 
 /* ---- Tuning and instrumentation (not part of the method) ---------------------------------- */
 
-/* Pair-kernel launch shape for one precision family and cluster-size class:
+/* Launch shape of the one-sided pair kernel (clusters of fewer than 4096 or more than 2^20 particles;
+ * the others have one fixed shape) for one precision family and cluster-size class:
  *   prec  NB_FP32 / NB_FP32C (share a kernel), NB_FP32DS, NB_FP64 or NB_FP32DL
  *   nclass 0: largest cluster < 2048 particles, 1: < 32768, 2: < 131072, 3: larger
  *   k     i-particles per lane; waves_per_group  wavefronts sharing the same i-particles, each
@@ -263,12 +269,13 @@ int nbody_get_tile(const nbody_ctx* ctx, int32_t prec, int32_t nclass, nbody_til
  * nbody_step_sym6 calls with nsteps >= 2 capture the kernels of up to 8 steps into a HIP graph, and
  * nbody_substeps calls with nrounds >= 2 capture their rounds, once per argument set (a change of
  * any pointer, dt, system layout or launch shape recaptures; 8 graphs are cached), and replay them
- * on the caller's stream.  Results are bitwise those of the direct launches.  Disabled automatically while per-kernel timing is on. */
+ * on the caller's stream (evaluations of more than four pair launches, N above about 200,000, are
+ * launched directly).  Results are bitwise those of the direct launches.  Disabled automatically while per-kernel timing is on. */
 int nbody_use_graphs(nbody_ctx* ctx, int enable);
 
-/* Per-kernel timing with HIP events recorded on the call's stream around every pair-kernel
- * launch (enable = 1) or off (0, the default).  nbody_timing_read returns the summed duration
- * in milliseconds and the number of timed launches since the last read, waiting for the
+/* Per-kernel timing with HIP events recorded on the call's stream around the pair kernels of every
+ * evaluation (enable = 1) or off (0, the default).  nbody_timing_read returns the summed duration
+ * in milliseconds and the number of timed evaluations since the last read, waiting for the
  * recorded events to complete; it resets the counters. */
 int nbody_timing_enable(nbody_ctx* ctx, int enable);
 int nbody_timing_read(nbody_ctx* ctx, double* ms_total, int64_t* launches);

@@ -30,7 +30,8 @@ __device__ __forceinline__ bool last_block_of_cluster(int* counter, int nchunks)
 constexpr int kPartials = 11;
 __global__ __launch_bounds__(kBlock) void k_update(Args a, int update) {
   __shared__ double sh[6][kBlock];
-  if (blockIdx.x == 0 && threadIdx.x == 0) *a.item_counter = 0;  // the pair kernel that follows starts at item 0
+  if (blockIdx.x == 0)  // the pair kernels that follow start at item 0
+    for (int q = threadIdx.x; q < a.ncounters; q += kBlock) a.item_counter[q] = 0;
   const Chunk ch = a.chunks[blockIdx.x];
   const DevCluster c = a.cl[ch.cluster];
   const int t = threadIdx.x;
@@ -197,10 +198,9 @@ __global__ __launch_bounds__(kBlock) void k_energy(Args a) {
 
 // Sum the partial sums of the j-ranges of split clusters in range order and finish each particle
 // (scale by G, galaxy field, store, optional kick, optional potential), as the pair kernel does for
-// clusters that are not split.  Pure-FP32 mode adds the ranges in FP32.
-__global__ __launch_bounds__(kBlock) void k_combine(Args a, int potmode, int kick) {
-  const Chunk ch = a.chunks[blockIdx.x];
-  const DevCluster c = a.cl[ch.cluster];
+// clusters that are not split.  Pure-FP32 mode adds the ranges in FP32.  Block (x, 0) takes chunk x.
+__device__ __forceinline__ void combine_split(const Args& a, const Chunk& ch, const DevCluster& c, int potmode,
+                                              int kick) {
   const int t = threadIdx.x;
   if ((c.split <= 1 && !(c.flags & kFlagDefer)) || t >= ch.count) return;
   const int li = ch.start + t;  // position in the cluster's (sorted) order
@@ -232,8 +232,89 @@ __global__ __launch_bounds__(kBlock) void k_combine(Args a, int potmode, int kic
   if (potmode && a.pot) a.pot[gi] = r32 ? (double)(-(float)a.G * (float)pt) : -a.G * pt;
 }
 
-hipError_t launch_combine(const Args& a, bool potmode, bool kick, hipStream_t s) {
-  hipLaunchKernelGGL(k_combine, dim3(a.nchunks), dim3(kBlock), 0, s, a, potmode ? 1 : 0, kick ? 1 : 0);
+// One band of the symmetric path (SymRows in nb_internal.h): every particle's rows of the band, and
+// the running sums of the bands before, in row order; after the last band the particle is finished.
+// HBM-bound (24 bytes per particle and row).  Q = 4 threads per particle, each taking every fourth
+// row, for clusters too small to fill the chip with one: block (x, y) then takes 64 particles of chunk
+// x, wave q the rows q, q + 4, ...; else block (x, 0) takes the chunk, one thread per particle.
+template <int NC>
+__device__ __forceinline__ void combine_sym(const Args& a, const Chunk& ch, const DevCluster& c, int band, int kick,
+                                            double (*sh)[4][64]) {
+  const SymRows rows = sym_rows(c.n, c.nseg, NC == 4, c.sym_doubles);
+  if (band >= rows.nbands) return;
+  const int Q = sym_sums(c.n);
+  if (Q == 1 && blockIdx.y) return;
+  const int t = threadIdx.x, q = Q == 1 ? 0 : t >> 6;
+  const int e = Q == 1 ? t : 64 * blockIdx.y + (t & 63);
+  const bool valid = e < ch.count;
+  const int li = ch.start + (valid ? e : 0), n = c.n;
+  const int r0 = rows.row0(band), r1 = rows.row1(band);
+  const bool last = band == rows.nbands - 1;
+  double* const base = a.sym + c.part_off;
+  double* const run = base + ((size_t)rows.cap + q) * NC * n + li;  // running sums (more than one band)
+  double sum[NC];
+#pragma unroll
+  for (int d = 0; d < NC; ++d) sum[d] = band ? run[(size_t)d * n] : 0.0;
+  constexpr int kBatch = 8;  // rows in flight per thread
+  const int first = r0 + ((q - r0) & (Q - 1));
+  for (int r = first; r < r1; r += kBatch * Q) {
+    double v[kBatch][NC];
+#pragma unroll
+    for (int b = 0; b < kBatch; ++b)
+#pragma unroll
+      for (int d = 0; d < NC; ++d)
+        v[b][d] = r + b * Q < r1 ? base[((size_t)(r + b * Q - r0) * NC + d) * n + li] : 0.0;
+#pragma unroll
+    for (int b = 0; b < kBatch; ++b)
+      if (r + b * Q < r1)
+#pragma unroll
+        for (int d = 0; d < NC; ++d) sum[d] += v[b][d];
+  }
+  if (!last) {
+    if (valid)
+#pragma unroll
+      for (int d = 0; d < NC; ++d) run[(size_t)d * n] = sum[d];
+    return;
+  }
+  if (Q > 1) {
+#pragma unroll
+    for (int d = 0; d < NC; ++d) sh[d][q][t & 63] = sum[d];
+    __syncthreads();
+    if (q) return;
+#pragma unroll
+    for (int d = 0; d < NC; ++d)
+      for (int s = 1; s < Q; ++s) sum[d] += sh[d][s][t];
+  }
+  if (!valid) return;
+  const double mc = a.mconst[ch.cluster];  // equal masses: the sums leave the mass out
+  if (mc != 0.0)
+#pragma unroll
+    for (int d = 0; d < NC; ++d) sum[d] *= mc;
+  const long long gi = particle_index(a, c, li);
+  const bool r32 = a.prec == NB_FP32;
+  finish_particle<true>(a, c, ch.cluster, gi, sum[0], sum[1], sum[2], r32, kick);
+  if constexpr (NC == 4) {
+    if (a.pot) a.pot[gi] = r32 ? (double)(-(float)a.G * (float)sum[3]) : -a.G * sum[3];
+  }
+}
+
+template <int NC>
+__global__ __launch_bounds__(kBlock) void k_combine(Args a, int band, int kick) {
+  __shared__ double sh[NC][4][64];
+  const Chunk ch = a.chunks[blockIdx.x];
+  const DevCluster c = a.cl[ch.cluster];
+  if (c.seg)
+    combine_sym<NC>(a, ch, c, band, kick, sh);
+  else if (band == 0 && blockIdx.y == 0)
+    combine_split(a, ch, c, NC == 4, kick);
+}
+
+hipError_t launch_combine(const Args& a, int band, bool potmode, bool kick, hipStream_t s) {
+  const dim3 grid(a.nchunks, a.sym ? 4 : 1);
+  if (potmode)
+    hipLaunchKernelGGL(k_combine<4>, grid, dim3(kBlock), 0, s, a, band, kick ? 1 : 0);
+  else
+    hipLaunchKernelGGL(k_combine<3>, grid, dim3(kBlock), 0, s, a, band, kick ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -1,4 +1,5 @@
-// Launch of the persistent pair kernel (kernels in kernels_pair_{f32,ds,f64,dl}.hip).
+// Launch of the pair kernels (one-sided: kernels_pair_{f32,ds,f64,dl}.hip, symmetric:
+// kernels_sym_{f32,ds,f64,dl}.hip).
 #include "nb_internal.h"
 
 namespace nb {
@@ -26,6 +27,15 @@ hipError_t launch_pair(const Args& a, const TileCfg& t, int grid, bool mask, boo
   if (!fn) return hipErrorInvalidValue;
   hipLaunchKernelGGL(fn, dim3(grid), dim3(kBlock), 0, s, a, kick ? 1 : 0);
   return hipGetLastError();
+}
+
+hipError_t launch_pair_sym(const Args& a, const SymBand& b, int grid, bool mask, bool potmode, hipStream_t s) {
+  switch (a.prec) {
+    case 4: return launch_sym_dl(a, b, grid, mask, potmode, s);
+    case 3: return launch_sym_f64(a, b, grid, mask, potmode, s);
+    case 2: return launch_sym_ds(a, b, grid, mask, potmode, s);
+    default: return launch_sym_f32(a, b, grid, mask, potmode, s);
+  }
 }
 
 }  // namespace nb

@@ -168,15 +168,36 @@ __global__ __launch_bounds__(kBlock) void k_rscatter(Args a, int src, int shift)
   }
 }
 
-// The FP64 state of the sorted order, so the pair kernel streams its j-tiles contiguously.
+// The FP64 state of the sorted order, so the pair kernels stream it contiguously; and for the
+// symmetric path, whose i-groups are the chunks, the frame of each group: the centre of its box and
+// (3/4 of the box diagonal)^2 with the margin of k_farflags.
 __global__ __launch_bounds__(kBlock) void k_gather(Args a) {
+  __shared__ double sh[6][kBlock];
   const Chunk ch = a.chunks[blockIdx.x];
   const DevCluster c = a.cl[ch.cluster];
   const int t = threadIdx.x;
-  if (t >= ch.count) return;
-  const long long l = c.off + ch.start + t;
-  const long long g = c.off + a.sval[1][l];
-  a.spos[l] = make_double4(a.pos[3 * g], a.pos[3 * g + 1], a.pos[3 * g + 2], a.mass[g]);
+  const bool valid = t < ch.count;
+  double x[3] = {0.0, 0.0, 0.0};
+  if (valid) {
+    const long long l = c.off + ch.start + t;
+    const long long g = c.off + a.sval[1][l];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) x[d] = a.pos[3 * g + d];
+    a.spos[l] = make_double4(x[0], x[1], x[2], a.mass[g]);
+  }
+  if (!c.seg) return;
+  double mn[3], mx[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    mn[d] = valid ? x[d] : INFINITY;
+    mx[d] = valid ? x[d] : -INFINITY;
+  }
+  block_minmax<3>(mn, mx, sh);
+  if (t == 0) {
+    const double dx = mx[0] - mn[0], dy = mx[1] - mn[1], dz = mx[2] - mn[2];
+    a.gbox[blockIdx.x] = make_double4(0.5 * (mn[0] + mx[0]), 0.5 * (mn[1] + mx[1]), 0.5 * (mn[2] + mx[2]),
+                                      (dx * dx + dy * dy + dz * dz) * (0.5625 * (1.0 + 1e-6)));
+  }
 }
 
 // Bounding boxes of the j-tiles of every range of every cluster (the tiles of T sorted sources the
@@ -341,6 +362,7 @@ hipError_t launch_sort(const Args& a, int B, hipStream_t s) {
   }
   // three passes: the sorted order is in buffer 1
   hipLaunchKernelGGL(k_gather, dim3(a.nchunks), dim3(kBlock), 0, s, a);
+  if (!a.nitems) return hipGetLastError();  // no cluster on the one-sided path
   const int waves = kBlock / 64;
   hipLaunchKernelGGL(k_tileboxes, dim3((a.ntboxes + waves - 1) / waves), dim3(kBlock), 0, s, a, B, a.ntboxes);
   hipLaunchKernelGGL(k_farflags, dim3((a.nitems + waves - 1) / waves), dim3(kBlock), 0, s, a);

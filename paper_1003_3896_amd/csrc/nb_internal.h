@@ -25,7 +25,7 @@ constexpr int kRadix = 1 << kRadixBits;
 struct DevCluster {
   long long off;       // first particle of the cluster in the concatenated arrays
   long long part_off;  // first row of the cluster's partial sums ([split][n] rows), when split > 1
-                       // or kFlagDefer
+                       // or kFlagDefer; symmetric path: first double of its rows in Args::sym
   int n;               // particles
   int flags;           // kFlagField | kFlagMaskSelf | kFlagDefer
   double eps2;         // eps^2 in FP64
@@ -37,7 +37,10 @@ struct DevCluster {
   int stile0;          // first sort tile of the cluster (NB_FP32DL)
   int nstiles;         // sort tiles of the cluster
   int tbox0;           // first j-tile box of the cluster (NB_FP32DL; room for split x ceil(jlen/128))
+  int seg;             // symmetric path: particles per segment (0: the cluster takes the one-sided path)
+  int nseg;            // symmetric path: segments
   int pad0;
+  long long sym_doubles;  // symmetric path: room for its rows (doubles)
 };
 constexpr int kFlagField = 1;     // add the galaxy field
 constexpr int kFlagMaskSelf = 2;  // eps == 0: the j = i term must be excluded explicitly
@@ -59,6 +62,83 @@ constexpr int kEnergyOut = 20;
 // j-tile t is far, and far enough for the expanded form of r^2).
 struct PairItem {
   int cluster, i0, js, flag0;
+};
+
+// ---- The symmetric path (pair_sym.h) ---------------------------------------------------------
+// Clusters of kSymMin to kSymMax particles.  Below, one cluster alone is too few items to fill the
+// chip (N = 3840 in FP64: 52 us per step one-sided); above, the rows would not fit the static scratch of
+// nbody_accel_noalloc beside what the one-sided path needs there (4 rows of 32 bytes per particle at
+// 2^20 particles against 4 ranges).
+constexpr int kSymMin = 4096, kSymMax = 1 << 20;
+constexpr int kSymBlocksPerCu = 2;  // of 8 waves: 4 per SIMD, an even number (pair_sym.h)
+// Particles per segment, a function of the cluster's size alone (its sums, and so its bits, depend on
+// it): small enough that one cluster has a few items per CU, large enough that the rows (48 bytes
+// written and read per particle and segment) stay a small part of the time (the combine pass took 8%
+// of the 512-cluster ensemble's step with 256 up to 16383, 4% with 512 from 8192 on).  The block's
+// waves cover a segment with their i-groups: 2 x 128, 2 x 256 or 4 x 256.
+__host__ __device__ inline int sym_segment(int n) { return n < 8192 ? 256 : n < 65536 ? 512 : 1024; }
+// Running sums the combine pass keeps per particle between bands (also its threads per particle): four
+// while there are too few particles to fill the chip with one thread each.
+__host__ __device__ inline int sym_sums(int n) { return n < 131072 ? 4 : 1; }
+
+// Rows of the partial-sum table.  Segment pairs are ordered by their circular distance delta = 0 ..
+// nseg / 2: the item (A, A + delta) writes row 2 delta - 1 of A's particles and row 2 delta of the
+// other's (row 0 of A for delta = 0; row nseg - 1 of both for delta = nseg / 2, which has half the
+// items), so every particle gets each of its nseg rows once.  When the room does not hold nseg rows,
+// the distances are taken in bands, each a launch of the pair kernel and one of the combine pass,
+// which adds the band's rows to the running sums; the order of the additions, and so the result, does
+// not depend on the room.
+struct SymRows {
+  int nseg, ndelta, d_first, d_next;  // distances; distances of the first band and of the later ones
+  int cap;                            // rows a band may use
+  int nbands;
+  __host__ __device__ int delta0(int band) const { return band ? d_first + d_next * (band - 1) : 0; }
+  __host__ __device__ int delta1(int band) const {
+    const int d = d_first + d_next * band;
+    return d < ndelta ? d : ndelta;
+  }
+  __host__ __device__ int row0(int band) const { return band ? 2 * delta0(band) - 1 : 0; }
+  __host__ __device__ int row1(int band) const {
+    const int r = 2 * delta1(band) - 1;
+    return r < nseg ? r : nseg;
+  }
+  __host__ __device__ int items(int band) const {
+    const int d1 = delta1(band), half = nseg % 2 == 0 && d1 == ndelta;
+    return (d1 - delta0(band)) * nseg - (half ? nseg / 2 : 0);
+  }
+};
+__host__ __device__ inline SymRows sym_rows(int n, int nseg, bool pot, long long doubles) {
+  SymRows r;
+  const long long row = (long long)(pot ? 4 : 3) * n;
+  r.nseg = nseg;
+  r.ndelta = nseg / 2 + 1;
+  if (row * nseg <= doubles) {
+    r.cap = nseg;
+    r.d_first = r.ndelta;
+    r.d_next = 1;
+    r.nbands = 1;
+  } else {
+    r.cap = (int)(doubles / row) - sym_sums(n);
+    r.d_first = (r.cap + 1) / 2;
+    r.d_next = r.cap / 2;
+    r.nbands = 1 + (r.ndelta - r.d_first + r.d_next - 1) / r.d_next;
+  }
+  return r;
+}
+
+// One band of a launch: its work counter, its items, and the clusters that take part.  The first
+// item of block b is item b; further ones come from the counter.
+struct SymEntry {
+  int first;    // the cluster's first item
+  int cluster;
+  int delta0;   // the band's first distance
+  int row0;     // and first row, of this cluster
+};
+struct SymBand {
+  int* counter;
+  const SymEntry* entries;  // [ncl]
+  int ncl, nitems, index;
+  int seg;  // 256: clusters with segments of 256 (two i-particles per lane), else the others
 };
 
 // Galaxy models (the values of the C interface's NB_GALAXY_* constants).
@@ -100,6 +180,9 @@ struct Args {
   double* mconst;      // [B] the common mass of a cluster whose masses are all equal, else 0
   double4* ref;        // [B] reference point of each cluster (centre of mass), w = total mass
   double4* part;       // partial sums (ax, ay, az, pot) of split clusters
+  double* sym;         // partial-sum rows of the symmetric path's clusters
+  double4* gbox;       // [nchunks] centre of each sorted chunk's box, w = (3/4 diagonal)^2 (NB_FP32DL)
+  int ncounters;       // work counters from item_counter on
   double* epart;       // [nchunks * kEnergySums] energy partials
   double* pot_ws;      // [Ntot] pair potential scratch for the energy pass
   double* eacc_ws;     // [Ntot * 3] internal accelerations of the energy pass
@@ -131,7 +214,14 @@ hipError_t launch_update(const Args& a, int B, bool update, hipStream_t s);
 hipError_t launch_pair(const Args& a, const TileCfg& t, int grid, bool mask, bool potmode, bool kick,
                        hipStream_t s);
 hipError_t launch_energy(const Args& a, hipStream_t s);
-hipError_t launch_combine(const Args& a, bool potmode, bool kick, hipStream_t s);
+// one band of the symmetric path (all of it when no cluster has more), and the one-sided clusters' sums
+// with band 0
+hipError_t launch_combine(const Args& a, int band, bool potmode, bool kick, hipStream_t s);
+hipError_t launch_pair_sym(const Args& a, const SymBand& b, int grid, bool mask, bool potmode, hipStream_t s);
+hipError_t launch_sym_f32(const Args& a, const SymBand& b, int grid, bool mask, bool pot, hipStream_t s);
+hipError_t launch_sym_ds(const Args& a, const SymBand& b, int grid, bool mask, bool pot, hipStream_t s);
+hipError_t launch_sym_dl(const Args& a, const SymBand& b, int grid, bool mask, bool pot, hipStream_t s);
+hipError_t launch_sym_f64(const Args& a, const SymBand& b, int grid, bool mask, bool pot, hipStream_t s);
 // Hilbert-curve sort: leaves the permutation in sval[1] and the sorted (x, y, z, m) in spos
 hipError_t launch_sort(const Args& a, int B, hipStream_t s);
 

@@ -77,8 +77,8 @@ void* g_scratch[kMaxDevices] = {};
 
 // Workspace layout of one system (depends on the system only, not on the tile choice).
 struct Layout {
-  size_t cl, chunks, stiles, items, counters, coef, ref, mconst, box, partials, epart, pot, eacc, part, skey, sval,
-      shist, sbase, spos, ibox, tbox, flags, total;
+  size_t cl, chunks, stiles, items, symtab, counters, coef, ref, mconst, box, partials, epart, pot, eacc, part, skey,
+      sval, shist, sbase, spos, ibox, tbox, flags, gbox, sym, total;
   size_t blob;  // bytes of the uploaded prefix [cl .. counters] (the coefficients follow it)
 };
 
@@ -90,7 +90,11 @@ struct Plan {
   int ntboxes = 0;  // j-tile box slots (NB_FP32DL only)
   int maxn = 0;
   bool anymask = false;
-  bool anysplit = false;  // some cluster is finished by the combine pass (split, or kFlagDefer)
+  bool anysplit = false;  // some one-sided cluster is finished by the combine pass (split, or kFlagDefer)
+  std::vector<int> sym;   // clusters on the symmetric path, largest first
+  int ndelta = 0;         // segment distances of the largest of them (bounds its bands)
+  size_t onesided = 0;    // workspace bytes if every cluster took the one-sided path
+  size_t onesided_blob = 0;
   std::vector<DevCluster> cl;
   std::vector<Chunk> chunks;
   std::vector<Chunk> stiles;
@@ -122,6 +126,17 @@ int split_of(int n) {
   int s = 1;
   while (s < smax && (long long)n * (2 * s) <= NB_SPLIT_CAP && n / (2 * s) >= NB_MIN_RANGE) s *= 2;
   return s;
+}
+
+// Room for the rows of the symmetric path: at most 64 rows per particle at a time (beside the running
+// sums), and at most the rows that leave a cluster of 2^18 particles inside the static scratch of the
+// no-allocation entry point; at least two rows per band, with the potential.
+constexpr int kSymRowsMax = 64;
+constexpr long long kSymBudget = 3LL * 34 << 18;  // doubles per cluster
+long long sym_doubles_min(int n) { return 4LL * n * (sym_sums(n) + 2); }
+long long sym_doubles_want(int n, int nseg) {
+  const long long rows = nseg <= kSymRowsMax ? nseg : kSymRowsMax + sym_sums(n);
+  return std::max(sym_doubles_min(n), std::min(3 * rows * n, kSymBudget));
 }
 
 // far-tile words of one item's j-range: two bits per tile, 16 tiles per word
@@ -223,8 +238,17 @@ int check_system(const nbody_system* sys) {
   return NB_OK;
 }
 
-Layout make_layout(int B, long long ntot, int nchunks, long long nitems_max, long long npart, int nstiles,
-                   long long nflagwords, long long ntiles) {
+// What a layout is made of: table and buffer lengths.
+struct Counts {
+  int B = 0, nchunks = 0, nstiles = 0;
+  long long ntot = 0;
+  long long nitems = 0, npart = 0, nflagwords = 0, ntiles = 0;  // one-sided path
+  long long nsymtab = 0, nbands = 0, symdoubles = 0;            // symmetric path (table entries, most bands)
+};
+
+Layout make_layout(const Counts& m) {
+  const int B = m.B, nchunks = m.nchunks, nstiles = m.nstiles;
+  const long long ntot = m.ntot, nitems_max = m.nitems, npart = m.npart, nflagwords = m.nflagwords, ntiles = m.ntiles;
   Layout L{};
   size_t o = 0;
   L.cl = o;
@@ -235,8 +259,10 @@ Layout make_layout(int B, long long ntot, int nchunks, long long nitems_max, lon
   o = align_up(o + sizeof(Chunk) * nstiles);
   L.items = o;
   o = align_up(o + sizeof(PairItem) * nitems_max);
-  L.counters = o;  // [B] chunk counters, the item counter, the finished-blocks counter
-  o = align_up(o + sizeof(int) * (B + 2));
+  L.symtab = o;  // entries of the symmetric path's bands
+  o = align_up(o + sizeof(SymEntry) * m.nsymtab);
+  L.counters = o;  // [B] chunk counters, the item counter, the bands' item counters
+  o = align_up(o + sizeof(int) * (B + 2 + m.nbands));
   L.coef = o;  // [kMaxRounds][B][3] per-cluster stage coefficients; only the used rounds are uploaded
   L.blob = o;
   o = align_up(o + sizeof(double) * 3 * (size_t)B * kMaxRounds);
@@ -272,23 +298,31 @@ Layout make_layout(int B, long long ntot, int nchunks, long long nitems_max, lon
   o = align_up(o + (nstiles ? sizeof(double) * 6 * (size_t)ntiles : 0));
   L.flags = o;  // far-tile bits of every work item's j-tiles (NB_FP32DL)
   o = align_up(o + (nstiles ? sizeof(unsigned) * (size_t)nflagwords : 0));
+  L.gbox = o;  // [nchunks] frame of each sorted chunk (NB_FP32DL, symmetric path)
+  o = align_up(o + (nstiles && m.nsymtab ? sizeof(double4) * (size_t)nchunks : 0));
+  L.sym = o;  // rows and running sums of the symmetric path
+  o = align_up(o + sizeof(double) * (size_t)m.symdoubles);
   L.total = o;
   return L;
 }
 
-// Validate the system and build the host tables.
-int build_plan(const nbody_system* sys, Plan& p) {
+// Validate the system and build the host tables.  limit: bytes the workspace may take (the
+// no-allocation scratch, which shrinks the symmetric path's room and so adds bands); 0 = no limit.
+int build_plan(const nbody_system* sys, Plan& p, size_t limit = 0) {
   int rc = check_system(sys);
   if (rc) return rc;
   p.B = sys->nclusters;
   p.cl.resize(p.B);
   p.chunks.clear();
   p.stiles.clear();
+  p.sym.clear();
+  p.ndelta = 0;
   const bool sorted = sys->prec == NB_FP32DL;
   p.maxn = 0;
   p.anymask = false;
   p.anysplit = false;
-  long long nitems_max = 0, npart = 0, nflagwords = 0, ntiles = 0;
+  Counts m, one;  // one: every cluster on the one-sided path
+  long long want = 0, least = 0;
   for (int b = 0; b < p.B; ++b) {
     DevCluster& c = p.cl[b];
     c.off = sys->offsets[b];
@@ -309,16 +343,34 @@ int build_plan(const nbody_system* sys, Plan& p) {
     c.split = split_of(c.n);
     c.jlen = (c.n + c.split - 1) / c.split;
     const bool via_combine = c.split > 1 || (c.flags & kFlagDefer);
-    c.part_off = via_combine ? npart : 0;
-    if (via_combine) {
-      npart += (long long)c.split * c.n;
-      p.anysplit = true;
+    // one-sided path: the smallest item tile is 64 particles; two far-tile bits per j-tile (of at
+    // least 128) of each item's range; j-tile boxes for split ranges of tiles of at least 128
+    const long long items = (long long)((c.n + 63) / 64) * c.split, part = via_combine ? (long long)c.split * c.n : 0;
+    const long long words = items * flag_words(c.jlen, 128), boxes = (long long)c.split * ((c.jlen + 127) / 128);
+    one.nitems += items;
+    one.npart += part;
+    one.nflagwords += words;
+    one.ntiles += boxes;
+    c.seg = c.nseg = 0;
+    c.sym_doubles = 0;
+    c.part_off = via_combine ? m.npart : 0;
+    c.tbox0 = (int)m.ntiles;
+    if (c.n >= kSymMin && c.n <= kSymMax) {
+      c.seg = sym_segment(c.n);
+      c.nseg = (c.n + c.seg - 1) / c.seg;
+      c.sym_doubles = sym_doubles_want(c.n, c.nseg);
+      want += c.sym_doubles;
+      least += sym_doubles_min(c.n);
+      p.sym.push_back(b);
+      p.ndelta = std::max(p.ndelta, c.nseg / 2 + 1);
+      m.nsymtab += c.nseg / 2 + 1;
+    } else {
+      m.nitems += items;
+      m.npart += part;
+      m.nflagwords += words;
+      m.ntiles += boxes;
+      p.anysplit |= via_combine;
     }
-    nitems_max += (long long)((c.n + 63) / 64) * c.split;  // the smallest item tile is 64 particles
-    // far-tile words of those items: two bits per j-tile of the item's range (tiles of at least 128)
-    nflagwords += (long long)((c.n + 63) / 64) * c.split * flag_words(c.jlen, 128);
-    c.tbox0 = (int)ntiles;  // the cluster's j-tile boxes: room for split ranges of tiles of >= 128
-    ntiles += (long long)c.split * ((c.jlen + 127) / 128);
     c.stile0 = (int)p.stiles.size();
     c.nstiles = 0;
     if (sorted)
@@ -331,19 +383,44 @@ int build_plan(const nbody_system* sys, Plan& p) {
   p.ntot = sys->offsets[p.B];
   p.nchunks = (int)p.chunks.size();
   p.nstiles = (int)p.stiles.size();
-  p.ntboxes = (int)ntiles;
-  p.L = make_layout(p.B, p.ntot, p.nchunks, nitems_max, npart, p.nstiles, nflagwords, ntiles);
+  p.ntboxes = (int)m.ntiles;
+  m.B = one.B = p.B;
+  m.ntot = one.ntot = p.ntot;
+  m.nchunks = one.nchunks = p.nchunks;
+  m.nstiles = one.nstiles = p.nstiles;
+  m.nbands = 2 * p.ndelta;
+  const Layout l1 = make_layout(one);
+  p.onesided = l1.total;
+  p.onesided_blob = l1.blob;
+  std::stable_sort(p.sym.begin(), p.sym.end(), [&](int x, int y) { return p.cl[x].n > p.cl[y].n; });
+  double share = 1.0;  // of each cluster's room above its least
+  if (limit) {
+    m.symdoubles = least;
+    const size_t base = make_layout(m).total + kAlign;
+    const double spare = base < limit ? (double)((limit - base) / sizeof(double)) : 0.0;
+    if ((double)(want - least) > spare) share = spare / (double)(want - least);
+  }
+  m.symdoubles = 0;
+  for (int b : p.sym) {
+    DevCluster& c = p.cl[b];
+    const long long lo = sym_doubles_min(c.n);
+    if (share < 1.0) c.sym_doubles = lo + (long long)(share * (double)(c.sym_doubles - lo));
+    c.part_off = m.symdoubles;
+    m.symdoubles += c.sym_doubles;
+  }
+  p.L = make_layout(m);
   return NB_OK;
 }
 
-// Pair work items for i-tiles of 64 K (4 / W) particles (item_tile), longest j-ranges first (ties
-// by cluster index).
+// Pair work items of the one-sided clusters for i-tiles of 64 K (4 / W) particles (item_tile), longest
+// j-ranges first (ties by cluster index).
 void make_items(const Plan& p, const TileCfg& t, std::vector<PairItem>& items, bool flags) {
   std::vector<int> order(p.B);
   for (int b = 0; b < p.B; ++b) order[b] = b;
   // longest items first: the cost of an item is its j-range length
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return p.cl[x].jlen > p.cl[y].jlen; });
   items.clear();
+  order.erase(std::remove_if(order.begin(), order.end(), [&](int b) { return p.cl[b].seg > 0; }), order.end());
   const int tile = item_tile(t);
   // j-range major: the blocks running at the same time stream the same sources through L2
   // in the local mode `flag0` is the item's first word of far-tile bits
@@ -395,7 +472,35 @@ struct Prepared {
   TileCfg tile{};
   int grid = 0;
   bool centred = false;
+  std::vector<SymBand> bands;  // launches of the symmetric path
 };
+
+// The bands of the symmetric path's clusters: item counts, and the table of which cluster an item
+// belongs to (written to `tab`, whose device copy is at `dev`).
+void make_bands(const Plan& p, bool pot, SymEntry* tab, const SymEntry* dev, int* counters,
+                std::vector<SymBand>& bands) {
+  std::vector<SymRows> rows;
+  int nbands = 0;
+  for (int k : p.sym) {
+    rows.push_back(sym_rows(p.cl[k].n, p.cl[k].nseg, pot, p.cl[k].sym_doubles));
+    nbands = std::max(nbands, rows.back().nbands);
+  }
+  size_t at = 0;
+  int* counter = counters;
+  for (int b = 0; b < nbands; ++b)
+    for (int seg : {512, 256}) {  // two launches where both kinds of segment are present
+      SymBand s{counter, dev + at, 0, 0, b, seg};
+      for (size_t k = 0; k < rows.size(); ++k) {
+        if (b >= rows[k].nbands || (p.cl[p.sym[k]].seg == 256) != (seg == 256)) continue;
+        tab[at++] = SymEntry{s.nitems, p.sym[k], rows[k].delta0(b), rows[k].row0(b)};
+        s.nitems += rows[k].items(b);
+        ++s.ncl;
+      }
+      if (!s.ncl) continue;
+      bands.push_back(s);
+      ++counter;
+    }
+}
 
 // The context's preallocated staging slot for `bytes` of tables: waits for its previous copy, never
 // allocates (the no-allocation entry point's path).
@@ -418,13 +523,13 @@ Slot* fixed_slot(nbody_ctx* ctx, size_t bytes, int* rc) {
 }
 
 int prepare(nbody_ctx* ctx, const nbody_system* sys, void* ws, size_t ws_bytes, const double* coef3,
-            Prepared& P, hipStream_t stream, int rounds = 1, bool fixed = false) {
+            Prepared& P, hipStream_t stream, bool pot = false, int rounds = 1, bool fixed = false) {
   Plan& p = ctx->plan;
   const int fam = family_of(sys->prec);
   const TileCfg t = ctx->tiles[fam][size_class(p.maxn)];
   std::vector<PairItem> items;
   make_items(p, t, items, p.nstiles > 0);
-  // host blob: [clusters | chunks | items | counters | coefficients of the used rounds]
+  // host blob: [clusters | chunks | sort tiles | items | bands | counters | coefficients of the used rounds]
   const Layout& L = p.L;
   const size_t coef_bytes = coef3 ? sizeof(double) * 3 * (size_t)p.B * rounds : 0;
   const size_t up = L.blob + coef_bytes;
@@ -435,6 +540,10 @@ int prepare(nbody_ctx* ctx, const nbody_system* sys, void* ws, size_t ws_bytes, 
   if (p.nstiles) memcpy(blob.data() + L.stiles, p.stiles.data(), sizeof(Chunk) * p.nstiles);
   memcpy(blob.data() + L.items, items.data(), sizeof(PairItem) * items.size());
   if (coef3) memcpy(blob.data() + L.coef, coef3, coef_bytes);
+  char* w = static_cast<char*>(ws);
+  if (!p.sym.empty())
+    make_bands(p, pot, reinterpret_cast<SymEntry*>(blob.data() + L.symtab),
+               reinterpret_cast<const SymEntry*>(w + L.symtab), reinterpret_cast<int*>(w + L.counters) + p.B + 1, P.bands);
   int rc = NB_OK;
   Slot* s = fixed ? fixed_slot(ctx, up, &rc) : get_slot(ctx, up, &rc);
   if (!s) return rc;
@@ -443,7 +552,6 @@ int prepare(nbody_ctx* ctx, const nbody_system* sys, void* ws, size_t ws_bytes, 
   HIP_TRY(hipEventRecord(s->ev, stream));
   s->used = true;
 
-  char* w = static_cast<char*>(ws);
   Args& a = P.a;
   a.cl = reinterpret_cast<const DevCluster*>(w + L.cl);
   a.chunks = reinterpret_cast<const Chunk*>(w + L.chunks);
@@ -452,7 +560,7 @@ int prepare(nbody_ctx* ctx, const nbody_system* sys, void* ws, size_t ws_bytes, 
   a.nitems = (int)items.size();
   a.chunk_counter = reinterpret_cast<int*>(w + L.counters);
   a.item_counter = reinterpret_cast<int*>(w + L.counters) + p.B;
-
+  a.ncounters = 1 + (int)P.bands.size();
   a.partials = reinterpret_cast<double*>(w + L.partials);
   a.box = reinterpret_cast<double*>(w + L.box);
   a.stiles = reinterpret_cast<const Chunk*>(w + L.stiles);
@@ -477,6 +585,8 @@ int prepare(nbody_ctx* ctx, const nbody_system* sys, void* ws, size_t ws_bytes, 
   a.pot_ws = reinterpret_cast<double*>(w + L.pot);
   a.eacc_ws = reinterpret_cast<double*>(w + L.eacc);
   a.part = reinterpret_cast<double4*>(w + L.part);
+  a.sym = p.sym.empty() ? nullptr : reinterpret_cast<double*>(w + L.sym);
+  a.gbox = reinterpret_cast<double4*>(w + L.gbox);
   a.coef = coef3 ? reinterpret_cast<double*>(w + L.coef) : nullptr;
   a.G = sys->G;
   a.gal = Galaxy{sys->galaxy.Mb,  sys->galaxy.ab,  sys->galaxy.Md,  sys->galaxy.ad,    sys->galaxy.bd,
@@ -501,7 +611,19 @@ hipEvent_t pool_event(nbody_ctx* ctx) {
   return e;
 }
 
-int pair(nbody_ctx* ctx, const Prepared& P, bool potmode, bool kick, hipStream_t s) {
+// One force evaluation of the current positions, optionally preceded by kick+drift and
+// followed by a kick (the substep).  Kernel sequence: update (kick, drift, centre of mass, work
+// counters) -> [sort] -> pair kernels of the one-sided and of the symmetric clusters -> [combine].
+// Per-kernel timing spans the pair kernels (with the combine passes between bands).
+int evaluate(nbody_ctx* ctx, Prepared& P, bool update, bool potmode, bool kick, hipStream_t s) {
+  hipError_t e;
+  const Plan& p = ctx->plan;
+  e = launch_update(P.a, p.B, update, s);  // also clears the pair kernels' work counters
+  if (e != hipSuccess) return fail(NB_ERR_HIP, "update kernel launch: %s", hipGetErrorString(e));
+  if (P.a.nstiles) {
+    e = launch_sort(P.a, p.B, s);  // also the work items' boxes and far-tile bits
+    if (e != hipSuccess) return fail(NB_ERR_HIP, "sort kernel launch: %s", hipGetErrorString(e));
+  }
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (ctx->timing) {
     e0 = pool_event(ctx);
@@ -509,29 +631,25 @@ int pair(nbody_ctx* ctx, const Prepared& P, bool potmode, bool kick, hipStream_t
     if (!e0 || !e1) return fail(NB_ERR_HIP, "event creation failed");
     HIP_TRY(hipEventRecord(e0, s));
   }
-  hipError_t e = launch_pair(P.a, P.tile, P.grid, ctx->plan.anymask, potmode, kick, s);
-  if (e != hipSuccess) return fail(NB_ERR_HIP, "pair kernel launch: %s", hipGetErrorString(e));
+  if (P.a.nitems) {
+    e = launch_pair(P.a, P.tile, P.grid, p.anymask, potmode, kick, s);
+    if (e != hipSuccess) return fail(NB_ERR_HIP, "pair kernel launch: %s", hipGetErrorString(e));
+  }
+  const int nbands = (int)P.bands.size();
+  for (int b = 0; b < nbands; ++b) {
+    const SymBand& band = P.bands[b];
+    e = launch_pair_sym(P.a, band, std::min(band.nitems, ctx->cus * kSymBlocksPerCu), p.anymask, potmode, s);
+    if (e != hipSuccess) return fail(NB_ERR_HIP, "pair kernel launch: %s", hipGetErrorString(e));
+    if (b == nbands - 1 || P.bands[b + 1].index == band.index) continue;
+    e = launch_combine(P.a, band.index, potmode, kick, s);
+    if (e != hipSuccess) return fail(NB_ERR_HIP, "combine kernel launch: %s", hipGetErrorString(e));
+  }
   if (ctx->timing) {
     HIP_TRY(hipEventRecord(e1, s));
     ctx->pending.emplace_back(e0, e1);
   }
-  return NB_OK;
-}
-
-// One force evaluation of the current positions, optionally preceded by kick+drift and
-// followed by a kick (the substep).  Kernel sequence: update (kick, drift, centre of mass, work
-// counter) -> pair -> [combine of split clusters].
-int evaluate(nbody_ctx* ctx, Prepared& P, bool update, bool potmode, bool kick, hipStream_t s) {
-  hipError_t e;
-  e = launch_update(P.a, ctx->plan.B, update, s);  // also clears the pair kernel's work counter
-  if (e != hipSuccess) return fail(NB_ERR_HIP, "update kernel launch: %s", hipGetErrorString(e));
-  if (P.a.nstiles) {
-    e = launch_sort(P.a, ctx->plan.B, s);  // also the work items' boxes and far-tile bits
-    if (e != hipSuccess) return fail(NB_ERR_HIP, "sort kernel launch: %s", hipGetErrorString(e));
-  }
-  int rc = pair(ctx, P, potmode, kick, s);
-  if (rc || !ctx->plan.anysplit) return rc;
-  e = launch_combine(P.a, potmode, kick, s);
+  if (!nbands && !p.anysplit) return NB_OK;
+  e = launch_combine(P.a, nbands ? P.bands.back().index : 0, potmode, kick, s);
   if (e != hipSuccess) return fail(NB_ERR_HIP, "combine kernel launch: %s", hipGetErrorString(e));
   return NB_OK;
 }
@@ -615,6 +733,11 @@ std::vector<unsigned char> graph_key(const Prepared& P, bool mask, int stages, F
   }
   put(&P.tile, sizeof P.tile);
   put(&P.grid, sizeof P.grid);
+  for (const SymBand& b : P.bands) {
+    put(&b.counter, sizeof b.counter);
+    put(&b.entries, sizeof b.entries);
+    put(&b.ncl, 4 * sizeof(int));
+  }
   put(&P.centred, sizeof P.centred);
   put(&mask, sizeof mask);
   put(&stages, sizeof stages);
@@ -634,6 +757,7 @@ void destroy_graph(StepGraph& g) {
 
 constexpr size_t kMaxGraphs = 8;
 constexpr int kGraphSteps = 8;
+constexpr int kGraphBands = 4;  // evaluations of more launches than this are long enough without a graph
 
 // Launch `replays` replays of the graph of `stages` evaluations (captured once per argument set on
 // the context's stream, and cached) on the caller's stream.
@@ -708,7 +832,7 @@ int run_steps(nbody_ctx* ctx, const nbody_system* sys, double* pos, double* vel,
     P.a.drift = (sym6 ? kSym6.d[k] : 1.0) * dt;
     P.a.kick_post = (k == stages - 1) ? (sym6 ? kSym6.k[7] : 0.5) * dt : 0.0;
   };
-  if (!ctx->graphs || ctx->timing || nsteps < 2) {
+  if (!ctx->graphs || ctx->timing || nsteps < 2 || (int)P.bands.size() > kGraphBands) {
     for (int32_t step = 0; step < nsteps; ++step)
       for (int k = 0; k < stages; ++k) {
         set_stage(k);
@@ -814,16 +938,27 @@ size_t nbody_workspace_bytes_max(int64_t max_particles, int32_t max_clusters) {
   // partial-sum rows: sum of split_c n_c over the clusters finished by the combine pass <=
   // min(16 n, B NB_SPLIT_CAP + n) (split_c n_c <= NB_SPLIT_CAP whenever split_c > 1, and an unsplit
   // cluster there, one in the second galaxy model, adds its n_c)
-  const long long nchunks = B + n / kChunk;
-  const long long nitems = kMaxSplit * (B + n / 64);
-  const long long npart = std::min(kMaxSplit * n, B * (long long)NB_SPLIT_CAP + n);
-  const long long nstiles = B + n / kSortTile;  // the sort of NB_FP32DL
+  Counts m;
+  m.B = (int)B;
+  m.ntot = n;
+  m.nchunks = (int)(B + n / kChunk);
+  m.nitems = kMaxSplit * (B + n / 64);
+  m.npart = std::min(kMaxSplit * n, B * (long long)NB_SPLIT_CAP + n);
+  m.nstiles = (int)(B + n / kSortTile);  // the sort of NB_FP32DL
   // far-tile words: sum over clusters of ceil(n_c/64) split_c ceil(jlen_c/2048)
   // <= (n/64 + B) (16 + (n + 16)/2048), since split_c <= 16 and split_c jlen_c <= n_c + split_c
-  const long long nflagwords = (n / 64 + B) * (kMaxSplit + (n + kMaxSplit) / 2048 + 1);
+  m.nflagwords = (n / 64 + B) * (kMaxSplit + (n + kMaxSplit) / 2048 + 1);
   // j-tile boxes: sum over clusters of split_c ceil(jlen_c/128) <= n/128 + 17 B
-  const long long ntiles = n / 128 + (kMaxSplit + 1) * B;
-  return make_layout((int)B, n, (int)nchunks, nitems, npart, (int)nstiles, nflagwords, ntiles).total;
+  m.ntiles = n / 128 + (kMaxSplit + 1) * B;
+  if (n >= kSymMin) {
+    // distances of a cluster: ceil(n_c / seg_c) / 2 + 1 <= n_c/512 + 2; room: at most kSymRowsMax + 4 rows
+    // of 3 doubles per particle, and at most the budget per cluster
+    const long long bs = std::min(B, n / kSymMin);  // clusters that can be on the symmetric path
+    m.nbands = 2 * (n / 512 + 2);
+    m.nsymtab = n / 512 + 2 * bs;
+    m.symdoubles = std::min(3 * (kSymRowsMax + 4) * n, bs * kSymBudget);
+  }
+  return make_layout(m).total;
 }
 
 int64_t nbody_interactions(const nbody_system* sys) {
@@ -857,7 +992,7 @@ int accel_call(nbody_ctx* ctx, const nbody_system* sys, const double* pos, const
   if (!g.ok) return fail(NB_ERR_HIP, "cannot select device %d", ctx->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
   Prepared P;
-  if ((rc = prepare(ctx, sys, ws, ws_bytes, nullptr, P, s, 1, fixed))) return rc;
+  if ((rc = prepare(ctx, sys, ws, ws_bytes, nullptr, P, s, pot != nullptr, 1, fixed))) return rc;
   P.a.pos = const_cast<double*>(pos);
   P.a.mass = mass;
   P.a.acc = acc;
@@ -883,14 +1018,17 @@ int nbody_accel_noalloc(nbody_ctx* ctx, const nbody_system* sys, const double* p
   // the limits are host-only checks of the system, made before anything else
   Plan local;
   Plan& p = ctx ? ctx->plan : local;
-  int rc = build_plan(sys, p);
+  int rc = build_plan(sys, p, kScratchBytes);
   if (rc) return rc;
-  if (p.L.total > kScratchBytes)
+  if (p.onesided > kScratchBytes)
     return fail(NB_ERR_ARG, "the system needs %zu bytes of workspace; the no-allocation scratch holds %zu",
-                p.L.total, kScratchBytes);
-  if (p.L.blob > kScratchTableBytes)
+                p.onesided, kScratchBytes);
+  if (p.onesided_blob > kScratchTableBytes)
     return fail(NB_ERR_ARG, "the system's tables take %zu bytes; the no-allocation staging buffer holds %zu",
-                p.L.blob, kScratchTableBytes);
+                p.onesided_blob, kScratchTableBytes);
+  if (p.L.total > kScratchBytes || p.L.blob > kScratchTableBytes)
+    return fail(NB_ERR_ARG, "the system does not fit the no-allocation scratch (%zu bytes, tables %zu)", p.L.total,
+                p.L.blob);
   if (!ctx) return fail(NB_ERR_ARG, "context is NULL");
   if (!ctx->scratch) return fail(NB_ERR_HIP, "device scratch address unknown");
   return accel_call(ctx, sys, pos, mass, acc, pot, ctx->scratch, kScratchBytes, stream, true);
@@ -913,7 +1051,7 @@ int nbody_substeps(nbody_ctx* ctx, const nbody_system* sys, double* pos, double*
   if (!g.ok) return fail(NB_ERR_HIP, "cannot select device %d", ctx->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
   Prepared P;
-  if ((rc = prepare(ctx, sys, ws, ws_bytes, coef, P, s, nrounds))) return rc;
+  if ((rc = prepare(ctx, sys, ws, ws_bytes, coef, P, s, false, nrounds))) return rc;
   P.a.pos = pos;
   P.a.vel = vel;
   P.a.acc = acc;
@@ -921,7 +1059,7 @@ int nbody_substeps(nbody_ctx* ctx, const nbody_system* sys, double* pos, double*
   P.a.pot = nullptr;
   double* base = P.a.coef;
   auto set_round = [&](int r) { P.a.coef = base + 3 * (size_t)B * r; };
-  if (!ctx->graphs || ctx->timing || nrounds < 2) {
+  if (!ctx->graphs || ctx->timing || nrounds < 2 || (int)P.bands.size() > kGraphBands) {
     for (int r = 0; r < nrounds; ++r) {
       set_round(r);
       if ((rc = evaluate(ctx, P, true, false, true, s))) return rc;
@@ -975,7 +1113,7 @@ int nbody_energy(nbody_ctx* ctx, const nbody_system* sys, const double* pos, con
   if (!g.ok) return fail(NB_ERR_HIP, "cannot select device %d", ctx->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
   Prepared P;
-  if ((rc = prepare(ctx, sys, ws, ws_bytes, nullptr, P, s))) return rc;
+  if ((rc = prepare(ctx, sys, ws, ws_bytes, nullptr, P, s, true))) return rc;
   P.a.pos = const_cast<double*>(pos);
   P.a.vel = const_cast<double*>(vel);
   P.a.mass = mass;

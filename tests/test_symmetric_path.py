@@ -1,0 +1,119 @@
+"""The symmetric pair path (clusters of 4096 to 2^20 particles): each unordered pair evaluated once, both
+accelerations kept.  Sizes at the edges of its segments (256 below 8192 particles, 512 below 65536,
+1024 from there), with remainders of one particle, odd and even numbers of segments, several bands of
+partial-sum rows, equal and unequal masses, eps = 0, batches that mix it with the one-sided path;
+against the oracle with the gates of gpu_helpers (derived there), and bitwise where only the room for
+the rows or the batch differs."""
+import numpy as np
+import pytest
+
+from paper_1003_3896_amd import inputs, nbody
+
+EDGES = [4095, 4096, 4097, 4353, 8191, 8192, 8705]
+
+
+def test_workspace_bound_at_segment_boundaries():
+    """Every size where the path, the segment length or the number of bands changes stays within the
+    batch-independent bound, alone and many times over, and no more room is asked for in one mode than
+    another (the local mode's sort buffers apart)."""
+    for n in EDGES + [16384, 65535, 65536, 131071, 131072, 262144, 1 << 20, (1 << 20) + 1]:
+        for sizes in ([n], [n] * 5, [n, 1, 300, n + 1]):
+            offs = np.concatenate([[0], np.cumsum(sizes)])
+            bound = nbody.nbody_workspace_bytes_max(int(offs[-1]), len(sizes))
+            ws = {p: nbody.nbody_workspace_bytes(None, nbody.System(offs, 1e-3, prec=p)) for p in nbody.PREC}
+            assert max(ws.values()) <= bound, (sizes, ws, bound)
+            assert ws["fp32"] == ws["fp32c"] == ws["fp32ds"] == ws["fp64"] <= ws["fp32dl"]
+
+
+def test_noalloc_accepts_what_the_one_sided_rows_fit():
+    """The no-allocation limits are those of the one-sided path's workspace: 32 bytes per particle and
+    range.  Systems just inside them reach the context check, systems beyond are rejected."""
+    for prec, inside, outside in (("fp64", [700000] * 2, [1 << 20, 500000]), ("fp32dl", [1400000], [1450000]),
+                                  ("fp64", [9000] * 100, [9000] * 120)):
+        for sizes, match in ((inside, "context is NULL"), (outside, "scratch")):
+            offs = np.concatenate([[0], np.cumsum(sizes)])
+            with pytest.raises(nbody.NBodyError, match=match):
+                nbody.nbody_accel_noalloc(None, nbody.System(offs, 1e-3, prec=prec), None, None, None, None, 0)
+
+
+def _cluster(n, seed, salpeter, field, eps):
+    p, v, m = inputs.plummer(n, seed, salpeter=salpeter)
+    if field:
+        p, v = inputs.on_orbit(p, v)
+    return inputs.single(p, v, m, eps, field)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec", ["fp64", "fp32ds", "fp32dl", "fp32c", "fp32"])
+@pytest.mark.parametrize("salpeter,eps", [(False, 1e-3), (True, 1e-3), (False, 0.0), (True, 0.0)])
+def test_edges_match_oracle(prec, salpeter, eps):
+    from gpu_helpers import TOL, TOL_MEDIAN, make_sim, oracle_reference, rel_errors, stats, torch_dev
+    torch_dev()
+    # one ragged batch: every edge size, small one-sided clusters between them, the field on every other
+    cl = []
+    for c, n in enumerate(EDGES):
+        cl.append(_cluster(n, 8100 + c, salpeter, c % 2 == 0 and eps > 0, eps))
+        cl.append(_cluster(65 + c, 8200 + c, salpeter, False, eps))
+    b = inputs.concat(cl)
+    sim = make_sim(b, prec)
+    a0 = sim.accel().cpu().numpy().copy()
+    a = sim.accel(pot=True).cpu().numpy()
+    pot = sim.pot.cpu().numpy()
+    assert np.array_equal(a0, a)  # the potential's own bands change nothing
+    ref, scale, rpot = oracle_reference(b, want_pot=True)
+    err = rel_errors(a, ref, scale)
+    print("\n[symmetric edges %s salpeter=%s eps=%g] %s" % (prec, salpeter, eps, stats(err)), flush=True)
+    assert err.max() <= TOL[prec] and np.median(err) <= TOL_MEDIAN[prec]
+    ptol = {"fp64": 1e-13, "fp32ds": 2e-6, "fp32dl": 2e-6, "fp32c": 1e-4, "fp32": 1e-4}[prec]
+    for c in range(b.B):
+        s = slice(b.offsets[c], b.offsets[c + 1])
+        assert np.abs(pot[s] - rpot[s]).max() <= ptol * np.abs(rpot[s]).max(), c
+    # a cluster alone is bitwise the cluster in the batch
+    for c in (2, 8):
+        s = slice(b.offsets[c], b.offsets[c + 1])
+        alone = make_sim(inputs.single(b.pos[s], b.vel[s], b.mass[s], b.eps[c], bool(b.field[c])), prec)
+        assert np.array_equal(alone.accel().cpu().numpy(), a[s]), c
+    sim.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [65535, 65536, 65537, 131072, 135169])
+def test_larger_segments_sampled_rows(n):
+    """512- and 1024-particle segments, an odd and an even number of them, one band and several."""
+    import oracle
+    from gpu_helpers import TOL, make_sim, rel_errors, stats, torch_dev
+    torch_dev()
+    b = _cluster(n, 8300, True, False, 1e-4)
+    rows = [(0, 48), (n // 2 - 24, n // 2 + 24), (n - 48, n)]
+    idx = np.concatenate([np.arange(r0, r1) for r0, r1 in rows])
+    ref, scale = zip(*(oracle.accel(b.pos, b.mass, 1.0, 1e-4, rows=r, want_abs=True) for r in rows))
+    for prec in ("fp64", "fp32dl", "fp32ds"):
+        sim = make_sim(b, prec)
+        a = sim.accel().cpu().numpy()
+        err = rel_errors(a[idx], np.concatenate(ref), np.concatenate(scale))
+        print("\n[symmetric N=%d %s] %s" % (n, prec, stats(err)), flush=True)
+        assert err.max() <= TOL[prec]
+        # reactions: the mass-weighted sum of all accelerations vanishes to the mode's rounding
+        mom = np.abs((b.mass[:, None] * a).sum(0)).max() / (b.mass[:, None] * np.abs(a)).sum()
+        assert mom < (1e-12 if prec == "fp64" else 1e-6)
+        sim.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec", ["fp64", "fp32dl"])
+def test_less_room_more_bands_same_bits(prec):
+    """In the no-allocation scratch the rows of these clusters take more bands than in the caller's
+    workspace: bitwise the same accelerations and potentials."""
+    from gpu_helpers import make_sim, torch_dev
+    torch = torch_dev()
+    b = inputs.concat([_cluster(200000, 8400, False, False, 1e-4), _cluster(65536, 8401, True, True, 1e-4),
+                       _cluster(5000, 8402, True, False, 1e-3)])
+    sim = make_sim(b, prec)
+    acc, pot = torch.zeros_like(sim.acc), torch.zeros_like(sim.pot)
+    for want in (True, False):
+        sim.accel(pot=want)
+        nbody.nbody_accel_noalloc(sim.ctx, sim.sys, sim.pos, sim.mass, acc, pot if want else None)
+        torch.cuda.synchronize()
+        assert torch.equal(acc, sim.acc)
+        assert torch.equal(pot, sim.pot)
+    sim.close()
