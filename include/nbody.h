@@ -45,7 +45,8 @@
  *              box; a j-tile all of whose sources lie at least 3/4 of the box diagonal from that
  *              centre is computed in FP32 on those local coordinates (coordinate-difference error
  *              at most 1.5 x 2^-22 relative), any other in double-single as NB_FP32DS.  Sums
- *              folded into FP64 per tile as in NB_FP32C.
+ *              folded into FP64 per tile as in NB_FP32C.  Clusters of fewer than 4096 particles,
+ *              nearly all of whose tiles would be near, are not sorted and run as NB_FP32DS.
  *
  * Errors
  *   Every function returns NB_OK (0) or a negative status.  All argument checks run on the host
@@ -251,7 +252,8 @@ const char* nbody_last_error(void);
  *   tile  j-records per LDS tile (128 or 256); FP32 partial sums are folded into FP64 after every
  *         tile/waves_per_group terms, so tile and waves_per_group change the last bits of FP32-mode
  *         results while k and blocks_per_cu never do (in NB_FP32DL k does too: it sets the work
- *         item whose bounding box the local coordinates are centred on)
+ *         item whose bounding box the local coordinates are centred on); 1 is taken in place of 2
+ *         where a batch has fewer than two items per compute unit
  *   blocks_per_cu  persistent blocks per compute unit (1..8)
  *   phased  FP32 families only: full tiles are evaluated in groups of 8 pair terms whose
  *         reciprocal square roots issue back to back (shapes (1,4,256), (2,2,256), (2,4,*));

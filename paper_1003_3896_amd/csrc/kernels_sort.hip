@@ -61,10 +61,10 @@ __device__ __forceinline__ unsigned cell(double x, double lo, double scale) {
 // Keys of one O(N) chunk: Hilbert index of the position's cell in the cluster's box (1024 cells
 // per axis), value = local index.
 __global__ __launch_bounds__(kBlock) void k_keys(Args a) {
-  const Chunk ch = a.chunks[blockIdx.x];
-  const DevCluster c = a.cl[ch.cluster];
+  const Chunk ch = load_chunk(a);
+  const DevCluster c = load_cluster(a, ch.cluster);
   const int t = threadIdx.x;
-  if (t >= ch.count) return;
+  if (t >= ch.count || !c.nstiles) return;
   const int l = ch.start + t;
   const long long g = c.off + l;
   const double* b = a.box + 6 * (size_t)ch.cluster;
@@ -97,6 +97,7 @@ __global__ __launch_bounds__(kBlock) void k_rhist(Args a, int src, int shift) {
 // digits in the whole cluster; their sum is the tile's first destination for the digit.
 __global__ __launch_bounds__(kRadix) void k_rscan(Args a) {
   const DevCluster c = a.cl[blockIdx.x];
+  if (!c.nstiles) return;
   const int d = threadIdx.x;
   int run = 0;
   constexpr int kBatch = 16;  // loads in flight per thread
@@ -173,9 +174,10 @@ __global__ __launch_bounds__(kBlock) void k_rscatter(Args a, int src, int shift)
 // (3/4 of the box diagonal)^2 with the margin of k_farflags.
 __global__ __launch_bounds__(kBlock) void k_gather(Args a) {
   __shared__ double sh[6][kBlock];
-  const Chunk ch = a.chunks[blockIdx.x];
-  const DevCluster c = a.cl[ch.cluster];
+  const Chunk ch = load_chunk(a);
+  const DevCluster c = load_cluster(a, ch.cluster);
   const int t = threadIdx.x;
+  if (!c.nstiles) return;
   const bool valid = t < ch.count;
   double x[3] = {0.0, 0.0, 0.0};
   if (valid) {

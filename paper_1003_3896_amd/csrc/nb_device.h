@@ -157,11 +157,33 @@ __device__ __forceinline__ double4 record64(const Args& a, long long gi) {
   return make_double4(a.pos[3 * gi], a.pos[3 * gi + 1], a.pos[3 * gi + 2], a.mass[gi]);
 }
 
-// Epilogue of one particle: scale by G, add the galaxy field (unless the pass wants the internal
-// acceleration alone), store, optional kick.  ALL_MODELS: as in galaxy_accel.
+// Reference point (centre of mass) and common mass of a small cluster, from its chunk partials (laid out
+// as k_update writes them): every wave reduces them by itself, which costs an item well under a
+// microsecond where a kernel of its own between the update and the pair kernel cost 3.3.
+constexpr int kPartials = 11;
+template <bool CENTRE>
+__device__ __forceinline__ double4 chunk_frame(const Args& a, const DevCluster& c, double& mc) {
+  static_assert(kSmallChunks <= 64, "one partial per lane");
+  const int lane = threadIdx.x & 63;
+  const bool has = lane < c.nchunks;
+  const double* p = a.partials + (size_t)(c.chunk0 + (has ? lane : 0)) * kPartials;
+  mc = __any(has && p[4] != 0.0) ? 0.0 : a.mass[c.off];
+  if (!CENTRE) return make_double4(0.0, 0.0, 0.0, 0.0);
+  double v[4];
+#pragma unroll
+  for (int d = 0; d < 4; ++d) v[d] = has ? p[d] : 0.0;
+#pragma unroll
+  for (int s = kSmallChunks / 2; s >= 1; s >>= 1)
+#pragma unroll
+    for (int d = 0; d < 4; ++d) v[d] += __shfl_xor(v[d], s);
+  return v[3] > 0.0 ? make_double4(v[0] / v[3], v[1] / v[3], v[2] / v[3], v[3]) : make_double4(0.0, 0.0, 0.0, 0.0);
+}
+
+// Acceleration of one particle from its pair sum: scale by G, add the galaxy field (unless the pass wants
+// the internal acceleration alone).  ALL_MODELS: as in galaxy_accel.
 template <bool ALL_MODELS>
-__device__ __forceinline__ void finish_particle(const Args& a, const DevCluster& c, int cluster, long long gi,
-                                                double ax, double ay, double az, bool round32, int kick) {
+__device__ __forceinline__ void finish_accel(const Args& a, const DevCluster& c, long long gi, double& ax, double& ay,
+                                             double& az, bool round32) {
   ax *= a.G;
   ay *= a.G;
   az *= a.G;
@@ -182,6 +204,14 @@ __device__ __forceinline__ void finish_particle(const Args& a, const DevCluster&
       az = (float)az;
     }
   }
+}
+
+// Epilogue of one particle: scale by G, add the galaxy field (unless the pass wants the internal
+// acceleration alone), store, optional kick.  ALL_MODELS: as in galaxy_accel.
+template <bool ALL_MODELS>
+__device__ __forceinline__ void finish_particle(const Args& a, const DevCluster& c, int cluster, long long gi,
+                                                double ax, double ay, double az, bool round32, int kick) {
+  finish_accel<ALL_MODELS>(a, c, gi, ax, ay, az, round32);
   if (a.acc) {
     a.acc[3 * gi] = ax;
     a.acc[3 * gi + 1] = ay;

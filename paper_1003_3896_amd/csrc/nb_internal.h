@@ -39,7 +39,7 @@ struct DevCluster {
   int tbox0;           // first j-tile box of the cluster (NB_FP32DL; room for split x ceil(jlen/128))
   int seg;             // symmetric path: particles per segment (0: the cluster takes the one-sided path)
   int nseg;            // symmetric path: segments
-  int pad0;
+  int pad0[2];
   long long sym_doubles;  // symmetric path: room for its rows (doubles)
 };
 constexpr int kFlagField = 1;     // add the galaxy field
@@ -154,6 +154,8 @@ struct Args {
   const DevCluster* cl;
   const Chunk* chunks;
   int nchunks;
+  int B;               // clusters
+  DevCluster cl0;      // the cluster when there is only one (load_cluster, load_chunk)
   const PairItem* items;
   int nitems;
   int* item_counter;   // dynamic work distribution of the persistent pair kernel
@@ -197,6 +199,8 @@ struct Args {
   int internal_only;  // 1: the pair pass stores the internal acceleration alone (no galaxy field)
   // uniform coefficients (used when coef == null)
   double kick_pre, drift, kick_post;
+  const double* coef_next;  // [B*3] or null, and uniform: those of the next stage, which the fused
+  double pre_next, drift_next;  // combine + update pass starts
   double G;
   Galaxy gal;
   int prec;  // NB_FP32 .. NB_FP64
@@ -209,14 +213,18 @@ struct TileCfg {
 };
 
 // Launchers (kernels_*.hip).  All return hipSuccess or the launch error.
-hipError_t launch_update(const Args& a, int B, bool update, hipStream_t s);
+// kick + drift (when update) and chunk partials; `finish`: the small clusters' sums first (small_cluster),
+// with the kick that ends their stage, then the next stage's kick and drift
+hipError_t launch_update(const Args& a, bool update, bool finish, hipStream_t s);
+// reference point, common mass and box of every cluster from the chunk partials
+hipError_t launch_reduce(const Args& a, int B, hipStream_t s);
 
 hipError_t launch_pair(const Args& a, const TileCfg& t, int grid, bool mask, bool potmode, bool kick,
                        hipStream_t s);
 hipError_t launch_energy(const Args& a, hipStream_t s);
-// one band of the symmetric path (all of it when no cluster has more), and the one-sided clusters' sums
-// with band 0
-hipError_t launch_combine(const Args& a, int band, bool potmode, bool kick, hipStream_t s);
+// one band of the symmetric path, and the sums of the one-sided clusters named
+enum CombineOneSided { kCombineNone, kCombineLarge, kCombineAll };
+hipError_t launch_combine(const Args& a, int band, bool potmode, bool kick, CombineOneSided which, hipStream_t s);
 hipError_t launch_pair_sym(const Args& a, const SymBand& b, int grid, bool mask, bool potmode, hipStream_t s);
 hipError_t launch_sym_f32(const Args& a, const SymBand& b, int grid, bool mask, bool pot, hipStream_t s);
 hipError_t launch_sym_ds(const Args& a, const SymBand& b, int grid, bool mask, bool pot, hipStream_t s);
@@ -236,9 +244,23 @@ PairFn pair_kernel_ds(const TileCfg& t, bool fold, bool mask, bool pot);
 PairFn pair_kernel_f64(const TileCfg& t, bool fold, bool mask, bool pot);
 PairFn pair_kernel_dl(const TileCfg& t, bool fold, bool mask, bool pot);
 
+// Cluster b, and this block's O(N) chunk.  A single cluster comes with the kernel arguments: the loads
+// from the tables would be one after the other, about a microsecond of every kernel of a small system.
+__device__ __forceinline__ DevCluster load_cluster(const Args& a, int b) { return a.B == 1 ? a.cl0 : a.cl[b]; }
+__device__ __forceinline__ Chunk load_chunk(const Args& a) {
+  if (a.B != 1) return a.chunks[blockIdx.x];
+  const int start = blockIdx.x * kChunk;
+  return Chunk{0, start, min(kChunk, a.cl0.n - start), 0};
+}
+
 // Index in the state arrays of the particle at (sorted) local position l of cluster c.
 __device__ __forceinline__ long long particle_index(const Args& a, const DevCluster& c, int l) {
-  return c.off + (a.perm ? a.perm[c.off + l] : l);
+  return c.off + (a.perm && c.nstiles ? a.perm[c.off + l] : l);
 }
+
+// Clusters of the one-sided path below the symmetric one: never sorted, at most kSmallChunks chunks, whose
+// partials the pair kernel reduces by itself (chunk_frame).
+constexpr int kSmallChunks = kSymMin / kChunk;
+__host__ __device__ inline bool small_cluster(const DevCluster& c) { return c.n < kSymMin; }
 
 }  // namespace nb

@@ -60,12 +60,16 @@ struct PairLds<FAM_F64, T> {
   double4 r[T];
 };
 
-// Takes the next work item for the whole block; returns -1 when none is left.
-__device__ __forceinline__ int next_item(const Args& a, int* s_item) {
+// Takes the next work item for the whole block (`it`: the one before, -1 at first); returns -1 when none
+// is left.  Block b begins with item b; only the items beyond the grid are handed out by the counter
+// (every block taking its first there cost the N = 1024 FP64 evaluation 1.5 us).
+__device__ __forceinline__ int next_item(const Args& a, int* s_item, int it) {
+  if (it < 0) return blockIdx.x < a.nitems ? blockIdx.x : -1;
+  if (gridDim.x >= a.nitems) return -1;
   __syncthreads();
-  if (threadIdx.x == 0) *s_item = atomicAdd(a.item_counter, 1);
+  if (threadIdx.x == 0) *s_item = gridDim.x + atomicAdd(a.item_counter, 1);
   __syncthreads();
-  const int it = *s_item;
+  it = *s_item;
   return it < a.nitems ? it : -1;
 }
 
@@ -84,11 +88,15 @@ __device__ __forceinline__ float wave_uniform(float x) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
 }
 __device__ __forceinline__ PairItem load_item(const Args& a, int it) {
+  if (a.B == 1) {  // j-range major, as the table has them
+    const int per = (a.cl0.n + a.item_tile - 1) / a.item_tile, js = it / per;
+    return PairItem{0, (it - js * per) * a.item_tile, js, 0};
+  }
   const PairItem p = a.items[it];
   return PairItem{wave_uniform(p.cluster), wave_uniform(p.i0), wave_uniform(p.js), 0};
 }
-__device__ __forceinline__ DevCluster load_cluster(const Args& a, int b) {
-  const DevCluster c = a.cl[b];
+__device__ __forceinline__ DevCluster uniform_cluster(const Args& a, int b) {
+  const DevCluster c = load_cluster(a, b);
   DevCluster u;
   u.off = wave_uniform(c.off);
   u.part_off = wave_uniform(c.part_off);
@@ -420,18 +428,28 @@ __device__ __forceinline__ void pair32_items(const Args& a, int kick) {
   float4* const s_ilo = reinterpret_cast<float4*>(red);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int grp = wave / W, sub = wave % W;
-  for (int it; (it = next_item(a, &s_item)) >= 0;) {
+  for (int it = -1; (it = next_item(a, &s_item, it)) >= 0;) {
     // (the local family keeps the work-item data in vector registers: its 80-VGPR build ran slower
     // with the extra scalar-register pressure)
     const PairItem item = LOC ? a.items[it] : load_item(a, it);
-    const DevCluster c = LOC ? a.cl[item.cluster] : load_cluster(a, item.cluster);
+    const DevCluster c = LOC ? a.cl[item.cluster] : uniform_cluster(a, item.cluster);
     // the frame the coordinates are taken in: the cluster's centre of mass, or in the local family the
     // centre of the item's i-particle box (computed with the item's far-tile bits by the sort pass)
-    const double4 r0 = LOC ? a.ibox[it] : a.ref[item.cluster];
+    // mc != 0: every mass of the cluster equals mc
+    double4 r0;
+    double mc;
+    if (LOC) {
+      r0 = a.ibox[it];
+      mc = a.mconst[item.cluster];
+    } else if (small_cluster(c)) {
+      r0 = chunk_frame<FAM != FAM_F32 || FOLD>(a, c, mc);
+      mc = wave_uniform(mc);
+    } else {
+      r0 = a.ref[item.cluster];
+      mc = wave_uniform(a.mconst[item.cluster]);
+    }
     const double4 ref = make_double4(wave_uniform(r0.x), wave_uniform(r0.y), wave_uniform(r0.z), 0.0);
     const int flag0 = LOC ? wave_uniform(item.flag0) : 0;
-    // != 0: every mass of the cluster equals mc
-    const double mc = LOC ? a.mconst[item.cluster] : wave_uniform(a.mconst[item.cluster]);
     const bool eq = mc != 0.0;
     const int ibase = item.i0 + grp * 64 * K + lane;
     float xi[K], yi[K], zi[K], xl[K], yl[K], zl[K], qi[K];
@@ -654,10 +672,14 @@ __global__ __launch_bounds__(kBlock) void k_pair64(Args a, int kick) {
   __shared__ int s_item;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int grp = wave / W, sub = wave % W;
-  for (int it; (it = next_item(a, &s_item)) >= 0;) {
-    const PairItem item = a.items[it];
-    const DevCluster c = a.cl[item.cluster];
-    const double mc = a.mconst[item.cluster];  // != 0: every mass of the cluster equals mc
+  for (int it = -1; (it = next_item(a, &s_item, it)) >= 0;) {
+    const PairItem item = load_item(a, it);
+    const DevCluster c = load_cluster(a, item.cluster);
+    double mc;  // != 0: every mass of the cluster equals mc
+    if (small_cluster(c))
+      chunk_frame<false>(a, c, mc);
+    else
+      mc = a.mconst[item.cluster];
     const bool eq = mc != 0.0;
     const int ibase = item.i0 + grp * 64 * K + lane;
     double xi[K], yi[K], zi[K], ax[K], ay[K], az[K], pt[K];

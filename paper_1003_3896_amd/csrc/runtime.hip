@@ -88,9 +88,10 @@ struct Plan {
   int nchunks = 0;
   int nstiles = 0;  // sort tiles (NB_FP32DL only)
   int ntboxes = 0;  // j-tile box slots (NB_FP32DL only)
-  int maxn = 0;
   bool anymask = false;
   bool anysplit = false;  // some one-sided cluster is finished by the combine pass (split, or kFlagDefer)
+  bool anylarge = false;  // some cluster is not small (small_cluster): it needs k_reduce, and its own combine
+  int maxn_small = 0, maxn_large = 0;  // largest one-sided cluster below and above the symmetric path
   std::vector<int> sym;   // clusters on the symmetric path, largest first
   int ndelta = 0;         // segment distances of the largest of them (bounds its bands)
   size_t onesided = 0;    // workspace bytes if every cluster took the one-sided path
@@ -261,7 +262,7 @@ Layout make_layout(const Counts& m) {
   o = align_up(o + sizeof(PairItem) * nitems_max);
   L.symtab = o;  // entries of the symmetric path's bands
   o = align_up(o + sizeof(SymEntry) * m.nsymtab);
-  L.counters = o;  // [B] chunk counters, the item counter, the bands' item counters
+  L.counters = o;  // [B] chunk counters, the item counters of the one-sided launches and of the bands
   o = align_up(o + sizeof(int) * (B + 2 + m.nbands));
   L.coef = o;  // [kMaxRounds][B][3] per-cluster stage coefficients; only the used rounds are uploaded
   L.blob = o;
@@ -318,9 +319,9 @@ int build_plan(const nbody_system* sys, Plan& p, size_t limit = 0) {
   p.sym.clear();
   p.ndelta = 0;
   const bool sorted = sys->prec == NB_FP32DL;
-  p.maxn = 0;
   p.anymask = false;
-  p.anysplit = false;
+  p.anysplit = p.anylarge = false;
+  p.maxn_small = p.maxn_large = 0;
   Counts m, one;  // one: every cluster on the one-sided path
   long long want = 0, least = 0;
   for (int b = 0; b < p.B; ++b) {
@@ -370,15 +371,18 @@ int build_plan(const nbody_system* sys, Plan& p, size_t limit = 0) {
       m.nflagwords += words;
       m.ntiles += boxes;
       p.anysplit |= via_combine;
+      (small_cluster(c) ? p.maxn_small : p.maxn_large) = std::max(small_cluster(c) ? p.maxn_small : p.maxn_large, c.n);
     }
+    p.anylarge |= !small_cluster(c);
+    if (sorted) m.nstiles += (c.n + kSortTile - 1) / kSortTile;
     c.stile0 = (int)p.stiles.size();
     c.nstiles = 0;
-    if (sorted)
+    // small clusters run the double-single kernels in the local mode: nearly all of their tiles are near
+    if (sorted && !small_cluster(c))
       for (int s = 0; s < c.n; s += kSortTile) {
         p.stiles.push_back(Chunk{b, s, std::min(kSortTile, c.n - s), 0});
         ++c.nstiles;
       }
-    p.maxn = std::max(p.maxn, c.n);
   }
   p.ntot = sys->offsets[p.B];
   p.nchunks = (int)p.chunks.size();
@@ -387,7 +391,7 @@ int build_plan(const nbody_system* sys, Plan& p, size_t limit = 0) {
   m.B = one.B = p.B;
   m.ntot = one.ntot = p.ntot;
   m.nchunks = one.nchunks = p.nchunks;
-  m.nstiles = one.nstiles = p.nstiles;
+  one.nstiles = m.nstiles;
   m.nbands = 2 * p.ndelta;
   const Layout l1 = make_layout(one);
   p.onesided = l1.total;
@@ -412,15 +416,14 @@ int build_plan(const nbody_system* sys, Plan& p, size_t limit = 0) {
   return NB_OK;
 }
 
-// Pair work items of the one-sided clusters for i-tiles of 64 K (4 / W) particles (item_tile), longest
-// j-ranges first (ties by cluster index).
-void make_items(const Plan& p, const TileCfg& t, std::vector<PairItem>& items, bool flags) {
-  std::vector<int> order(p.B);
-  for (int b = 0; b < p.B; ++b) order[b] = b;
+// Appends the pair work items of the one-sided clusters below (small) or above the symmetric path, for
+// i-tiles of 64 K (4 / W) particles (item_tile), longest j-ranges first (ties by cluster index).
+void make_items(const Plan& p, const TileCfg& t, std::vector<PairItem>& items, bool small, bool flags) {
+  std::vector<int> order;
+  for (int b = 0; b < p.B; ++b)
+    if (!p.cl[b].seg && small_cluster(p.cl[b]) == small) order.push_back(b);
   // longest items first: the cost of an item is its j-range length
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return p.cl[x].jlen > p.cl[y].jlen; });
-  items.clear();
-  order.erase(std::remove_if(order.begin(), order.end(), [&](int b) { return p.cl[b].seg > 0; }), order.end());
   const int tile = item_tile(t);
   // j-range major: the blocks running at the same time stream the same sources through L2
   // in the local mode `flag0` is the item's first word of far-tile bits
@@ -467,10 +470,14 @@ Slot* get_slot(nbody_ctx* ctx, size_t bytes, int* rc) {
 }
 
 // Everything a call needs after validation: device tables uploaded, Args filled.
-struct Prepared {
-  Args a{};
+struct OneSided {  // a launch of a one-sided pair kernel
   TileCfg tile{};
-  int grid = 0;
+  int first = 0, nitems = 0;  // its items in the table
+  int prec = 0;               // the mode whose kernel it runs
+};
+struct Prepared {
+  Args a{};  // items, nitems, item_tile and jtile: those of the large one-sided clusters
+  OneSided large, small;
   bool centred = false;
   std::vector<SymBand> bands;  // launches of the symmetric path
 };
@@ -525,10 +532,26 @@ Slot* fixed_slot(nbody_ctx* ctx, size_t bytes, int* rc) {
 int prepare(nbody_ctx* ctx, const nbody_system* sys, void* ws, size_t ws_bytes, const double* coef3,
             Prepared& P, hipStream_t stream, bool pot = false, int rounds = 1, bool fixed = false) {
   Plan& p = ctx->plan;
-  const int fam = family_of(sys->prec);
-  const TileCfg t = ctx->tiles[fam][size_class(p.maxn)];
   std::vector<PairItem> items;
-  make_items(p, t, items, p.nstiles > 0);
+  OneSided &lg = P.large, &sm = P.small;
+  lg.prec = sys->prec;
+  lg.tile = ctx->tiles[family_of(lg.prec)][size_class(p.maxn_large)];
+  if (p.maxn_large) make_items(p, lg.tile, items, false, sys->prec == NB_FP32DL);
+  lg.nitems = sm.first = (int)items.size();
+  sm.prec = sys->prec == NB_FP32DL ? NB_FP32DS : sys->prec;
+  sm.tile = ctx->tiles[family_of(sys->prec)][size_class(p.maxn_small)];
+  if (p.maxn_small) {
+    make_items(p, sm.tile, items, true, false);
+    // fewer than two items per CU: halves of them fill the chip better (the i-particles per lane do not
+    // change a result)
+    if ((int)items.size() - sm.first < 2 * ctx->cus && sm.tile.k == 2) {
+      sm.tile.k = 1;
+      sm.tile.phase = 0;
+      items.resize(sm.first);
+      make_items(p, sm.tile, items, true, false);
+    }
+  }
+  sm.nitems = (int)items.size() - sm.first;
   // host blob: [clusters | chunks | sort tiles | items | bands | counters | coefficients of the used rounds]
   const Layout& L = p.L;
   const size_t coef_bytes = coef3 ? sizeof(double) * 3 * (size_t)p.B * rounds : 0;
@@ -543,7 +566,7 @@ int prepare(nbody_ctx* ctx, const nbody_system* sys, void* ws, size_t ws_bytes, 
   char* w = static_cast<char*>(ws);
   if (!p.sym.empty())
     make_bands(p, pot, reinterpret_cast<SymEntry*>(blob.data() + L.symtab),
-               reinterpret_cast<const SymEntry*>(w + L.symtab), reinterpret_cast<int*>(w + L.counters) + p.B + 1, P.bands);
+               reinterpret_cast<const SymEntry*>(w + L.symtab), reinterpret_cast<int*>(w + L.counters) + p.B + 2, P.bands);
   int rc = NB_OK;
   Slot* s = fixed ? fixed_slot(ctx, up, &rc) : get_slot(ctx, up, &rc);
   if (!s) return rc;
@@ -556,11 +579,13 @@ int prepare(nbody_ctx* ctx, const nbody_system* sys, void* ws, size_t ws_bytes, 
   a.cl = reinterpret_cast<const DevCluster*>(w + L.cl);
   a.chunks = reinterpret_cast<const Chunk*>(w + L.chunks);
   a.nchunks = p.nchunks;
+  a.B = p.B;
+  a.cl0 = p.cl[0];
   a.items = reinterpret_cast<const PairItem*>(w + L.items);
-  a.nitems = (int)items.size();
+  a.nitems = lg.nitems;
   a.chunk_counter = reinterpret_cast<int*>(w + L.counters);
   a.item_counter = reinterpret_cast<int*>(w + L.counters) + p.B;
-  a.ncounters = 1 + (int)P.bands.size();
+  a.ncounters = 2 + (int)P.bands.size();
   a.partials = reinterpret_cast<double*>(w + L.partials);
   a.box = reinterpret_cast<double*>(w + L.box);
   a.stiles = reinterpret_cast<const Chunk*>(w + L.stiles);
@@ -577,8 +602,8 @@ int prepare(nbody_ctx* ctx, const nbody_system* sys, void* ws, size_t ws_bytes, 
   a.tbox = p.nstiles ? reinterpret_cast<double*>(w + L.tbox) : nullptr;
   a.ntboxes = p.nstiles ? p.ntboxes : 0;
   a.farflags = p.nstiles ? reinterpret_cast<unsigned*>(w + L.flags) : nullptr;
-  a.item_tile = item_tile(t);
-  a.jtile = t.tile;
+  a.item_tile = item_tile(lg.tile);
+  a.jtile = lg.tile.tile;
   a.mconst = reinterpret_cast<double*>(w + L.mconst);
   a.ref = reinterpret_cast<double4*>(w + L.ref);
   a.epart = reinterpret_cast<double*>(w + L.epart);
@@ -593,8 +618,6 @@ int prepare(nbody_ctx* ctx, const nbody_system* sys, void* ws, size_t ws_bytes, 
                  sys->galaxy.vh,  sys->galaxy.dh,  sys->galaxy.Mbh, sys->galaxy.ebh,   sys->galaxy.model,
                  sys->galaxy.Mh,  sys->galaxy.ah,  sys->galaxy.rcut};
   a.prec = sys->prec;
-  P.tile = t;
-  P.grid = std::max(1, std::min(a.nitems, ctx->cus * t.bpc));
   P.centred = sys->prec == NB_FP32C || sys->prec == NB_FP32DS || sys->prec == NB_FP32DL;
   (void)ws_bytes;
   return NB_OK;
@@ -611,15 +634,41 @@ hipEvent_t pool_event(nbody_ctx* ctx) {
   return e;
 }
 
-// One force evaluation of the current positions, optionally preceded by kick+drift and
-// followed by a kick (the substep).  Kernel sequence: update (kick, drift, centre of mass, work
-// counters) -> [sort] -> pair kernels of the one-sided and of the symmetric clusters -> [combine].
-// Per-kernel timing spans the pair kernels (with the combine passes between bands).
-int evaluate(nbody_ctx* ctx, Prepared& P, bool update, bool potmode, bool kick, hipStream_t s) {
+int pair_launch(nbody_ctx* ctx, const Prepared& P, const OneSided& o, int counter, bool potmode, bool kick,
+                hipStream_t s) {
+  if (!o.nitems) return NB_OK;
+  Args a = P.a;
+  a.items += o.first;
+  a.nitems = o.nitems;
+  a.item_counter += counter;
+  a.item_tile = item_tile(o.tile);
+  if (o.prec != a.prec) {  // small clusters of the local mode: unsorted, in the double-single kernel
+    a.prec = o.prec;
+    a.spos = nullptr;
+  }
+  const int grid = std::max(1, std::min(o.nitems, ctx->cus * o.tile.bpc));
+  const hipError_t e = launch_pair(a, o.tile, grid, ctx->plan.anymask, potmode, kick, s);
+  if (e != hipSuccess) return fail(NB_ERR_HIP, "pair kernel launch: %s", hipGetErrorString(e));
+  return NB_OK;
+}
+
+// The last (or only) combine pass of an evaluation.
+int combine(const Prepared& P, bool potmode, bool kick, bool small, hipStream_t s) {
+  const hipError_t e = launch_combine(P.a, P.bands.empty() ? 0 : P.bands.back().index, potmode, kick,
+                                      small ? kCombineAll : kCombineLarge, s);
+  if (e != hipSuccess) return fail(NB_ERR_HIP, "combine kernel launch: %s", hipGetErrorString(e));
+  return NB_OK;
+}
+
+// The pair sums of the positions that an update pass has just left (and reduced to chunk partials):
+// [reference points -> sort] -> pair kernels of the one-sided and of the symmetric clusters, the latter
+// with a combine pass after every band but the last.  Per-kernel timing spans the pair kernels.
+int pair_pass(nbody_ctx* ctx, Prepared& P, bool potmode, bool kick, hipStream_t s) {
   hipError_t e;
   const Plan& p = ctx->plan;
-  e = launch_update(P.a, p.B, update, s);  // also clears the pair kernels' work counters
-  if (e != hipSuccess) return fail(NB_ERR_HIP, "update kernel launch: %s", hipGetErrorString(e));
+  int rc;
+  if (p.anylarge && (e = launch_reduce(P.a, p.B, s)) != hipSuccess)
+    return fail(NB_ERR_HIP, "reduce kernel launch: %s", hipGetErrorString(e));
   if (P.a.nstiles) {
     e = launch_sort(P.a, p.B, s);  // also the work items' boxes and far-tile bits
     if (e != hipSuccess) return fail(NB_ERR_HIP, "sort kernel launch: %s", hipGetErrorString(e));
@@ -631,26 +680,60 @@ int evaluate(nbody_ctx* ctx, Prepared& P, bool update, bool potmode, bool kick, 
     if (!e0 || !e1) return fail(NB_ERR_HIP, "event creation failed");
     HIP_TRY(hipEventRecord(e0, s));
   }
-  if (P.a.nitems) {
-    e = launch_pair(P.a, P.tile, P.grid, p.anymask, potmode, kick, s);
-    if (e != hipSuccess) return fail(NB_ERR_HIP, "pair kernel launch: %s", hipGetErrorString(e));
-  }
+  if ((rc = pair_launch(ctx, P, P.large, 0, potmode, kick, s))) return rc;
+  if ((rc = pair_launch(ctx, P, P.small, 1, potmode, kick, s))) return rc;
   const int nbands = (int)P.bands.size();
   for (int b = 0; b < nbands; ++b) {
     const SymBand& band = P.bands[b];
     e = launch_pair_sym(P.a, band, std::min(band.nitems, ctx->cus * kSymBlocksPerCu), p.anymask, potmode, s);
     if (e != hipSuccess) return fail(NB_ERR_HIP, "pair kernel launch: %s", hipGetErrorString(e));
     if (b == nbands - 1 || P.bands[b + 1].index == band.index) continue;
-    e = launch_combine(P.a, band.index, potmode, kick, s);
+    e = launch_combine(P.a, band.index, potmode, kick, kCombineNone, s);
     if (e != hipSuccess) return fail(NB_ERR_HIP, "combine kernel launch: %s", hipGetErrorString(e));
   }
   if (ctx->timing) {
     HIP_TRY(hipEventRecord(e1, s));
     ctx->pending.emplace_back(e0, e1);
   }
-  if (!nbands && !p.anysplit) return NB_OK;
-  e = launch_combine(P.a, nbands ? P.bands.back().index : 0, potmode, kick, s);
-  if (e != hipSuccess) return fail(NB_ERR_HIP, "combine kernel launch: %s", hipGetErrorString(e));
+  return NB_OK;
+}
+
+// One force evaluation of the current positions (no integrator stage).
+int evaluate(nbody_ctx* ctx, Prepared& P, bool potmode, hipStream_t s) {
+  hipError_t e = launch_update(P.a, false, false, s);  // also clears the pair kernels' work counters
+  if (e != hipSuccess) return fail(NB_ERR_HIP, "update kernel launch: %s", hipGetErrorString(e));
+  int rc = pair_pass(ctx, P, potmode, false, s);
+  if (rc || (P.bands.empty() && !ctx->plan.anysplit)) return rc;
+  return combine(P, potmode, false, true, s);
+}
+
+// `stages` consecutive integrator stages (set_stage(k) sets the coefficients of stage k in P.a): each is
+// kick + drift, an evaluation and a kick.  Between two stages one pass ends the first for the small
+// clusters and starts the second; the others are finished by a combine pass before it.
+template <class F>
+int run_stages(nbody_ctx* ctx, Prepared& P, int stages, F& set_stage, hipStream_t s) {
+  hipError_t e;
+  int rc;
+  const bool combined = !P.bands.empty() || ctx->plan.anysplit;
+  set_stage(0);
+  e = launch_update(P.a, true, false, s);
+  if (e != hipSuccess) return fail(NB_ERR_HIP, "update kernel launch: %s", hipGetErrorString(e));
+  for (int k = 0; k < stages; ++k) {
+    const bool last = k == stages - 1;
+    if (!last) {
+      set_stage(k + 1);
+      P.a.coef_next = P.a.coef;
+      P.a.pre_next = P.a.kick_pre;
+      P.a.drift_next = P.a.drift;
+    }
+    set_stage(k);
+    const bool kick = P.a.coef != nullptr || P.a.kick_post != 0.0;
+    if ((rc = pair_pass(ctx, P, false, kick, s))) return rc;
+    if (combined && (last || ctx->plan.anylarge) && (rc = combine(P, false, kick, last, s))) return rc;
+    if (last) return NB_OK;
+    e = launch_update(P.a, true, true, s);
+    if (e != hipSuccess) return fail(NB_ERR_HIP, "update kernel launch: %s", hipGetErrorString(e));
+  }
   return NB_OK;
 }
 
@@ -731,8 +814,8 @@ std::vector<unsigned char> graph_key(const Prepared& P, bool mask, int stages, F
       put(&a.prec, sizeof(int));
     }
   }
-  put(&P.tile, sizeof P.tile);
-  put(&P.grid, sizeof P.grid);
+  put(&P.large, sizeof P.large);
+  put(&P.small, sizeof P.small);
   for (const SymBand& b : P.bands) {
     put(&b.counter, sizeof b.counter);
     put(&b.entries, sizeof b.entries);
@@ -773,14 +856,11 @@ int replay_graph(nbody_ctx* ctx, Prepared& P, int stages, F& set_stage, int32_t 
   if (hit == gs.size()) {
     StepGraph g;
     HIP_TRY(hipStreamBeginCapture(ctx->gstream, hipStreamCaptureModeThreadLocal));
-    for (int k = 0; k < stages; ++k) {
-      set_stage(k);
-      if ((rc = evaluate(ctx, P, true, false, P.a.coef != nullptr || P.a.kick_post != 0.0, ctx->gstream))) {
-        hipGraph_t dead = nullptr;
-        (void)hipStreamEndCapture(ctx->gstream, &dead);
-        if (dead) (void)hipGraphDestroy(dead);
-        return rc;
-      }
+    if ((rc = run_stages(ctx, P, stages, set_stage, ctx->gstream))) {
+      hipGraph_t dead = nullptr;
+      (void)hipStreamEndCapture(ctx->gstream, &dead);
+      if (dead) (void)hipGraphDestroy(dead);
+      return rc;
     }
     HIP_TRY(hipStreamEndCapture(ctx->gstream, &g.graph));
     HIP_TRY(hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0));
@@ -832,17 +912,15 @@ int run_steps(nbody_ctx* ctx, const nbody_system* sys, double* pos, double* vel,
     P.a.drift = (sym6 ? kSym6.d[k] : 1.0) * dt;
     P.a.kick_post = (k == stages - 1) ? (sym6 ? kSym6.k[7] : 0.5) * dt : 0.0;
   };
+  auto set_multi = [&](int k) { set_stage(k % stages); };
   if (!ctx->graphs || ctx->timing || nsteps < 2 || (int)P.bands.size() > kGraphBands) {
-    for (int32_t step = 0; step < nsteps; ++step)
-      for (int k = 0; k < stages; ++k) {
-        set_stage(k);
-        if ((rc = evaluate(ctx, P, true, false, k == stages - 1, s))) return rc;
-      }
+    const int most = (1 << 30) / stages;  // stages are counted in 32 bits
+    for (int32_t left = nsteps; left > 0; left -= most)
+      if ((rc = run_stages(ctx, P, std::min<int32_t>(left, most) * stages, set_multi, s))) return rc;
     return NB_OK;
   }
   // one graph holds up to kGraphSteps steps (graph launches cost more than a few kernel launches)
   const int gsteps = std::min<int>(nsteps, kGraphSteps);
-  auto set_multi = [&](int k) { set_stage(k % stages); };
   if ((rc = replay_graph(ctx, P, gsteps * stages, set_multi, nsteps / gsteps, s))) return rc;
   if (nsteps % gsteps) return replay_graph(ctx, P, (nsteps % gsteps) * stages, set_multi, 1, s);
   return NB_OK;
@@ -998,7 +1076,7 @@ int accel_call(nbody_ctx* ctx, const nbody_system* sys, const double* pos, const
   P.a.acc = acc;
   P.a.pot = pot;
   P.a.vel = nullptr;
-  return evaluate(ctx, P, false, pot != nullptr, false, s);
+  return evaluate(ctx, P, pot != nullptr, s);
 }
 
 }  // namespace
@@ -1059,13 +1137,8 @@ int nbody_substeps(nbody_ctx* ctx, const nbody_system* sys, double* pos, double*
   P.a.pot = nullptr;
   double* base = P.a.coef;
   auto set_round = [&](int r) { P.a.coef = base + 3 * (size_t)B * r; };
-  if (!ctx->graphs || ctx->timing || nrounds < 2 || (int)P.bands.size() > kGraphBands) {
-    for (int r = 0; r < nrounds; ++r) {
-      set_round(r);
-      if ((rc = evaluate(ctx, P, true, false, true, s))) return rc;
-    }
-    return NB_OK;
-  }
+  if (!ctx->graphs || ctx->timing || nrounds < 2 || (int)P.bands.size() > kGraphBands)
+    return run_stages(ctx, P, nrounds, set_round, s);
   return replay_graph(ctx, P, nrounds, set_round, 1, s);
 }
 
@@ -1121,7 +1194,7 @@ int nbody_energy(nbody_ctx* ctx, const nbody_system* sys, const double* pos, con
   P.a.internal_only = 1;
   P.a.pot = P.a.pot_ws;
   P.a.eout = out;
-  if ((rc = evaluate(ctx, P, false, true, false, s))) return rc;
+  if ((rc = evaluate(ctx, P, true, s))) return rc;
   hipError_t e = launch_energy(P.a, s);
   if (e != hipSuccess) return fail(NB_ERR_HIP, "energy kernel launch: %s", hipGetErrorString(e));
   return NB_OK;
