@@ -134,8 +134,9 @@ void nbody_destroy(nbody_ctx* ctx);
 
 /* Bytes of device workspace the calls below need for `sys` (0 if `sys` is invalid; then
  * nbody_last_error() says why): 32 bytes per particle; for clusters of 4096 to 2^20 particles
- * 24 bytes per particle and segment (segments of 256 particles below 8192, 512 below 65536, 1024
- * from there), for at most 68 segments at a time and at most 204 MiB per cluster; for the others 32
+ * 32 bytes per particle and segment (segments of 256 particles below 8192, 512 below 131072, 1024 from
+ * there) but at most 3360 bytes per particle, 204 MiB below 2^18 particles and 816 bytes per particle
+ * above; for the others 32
  * bytes per particle and j-range where the sums are split into several source ranges (a cluster of N
  * particles has about 2^22/N ranges, a power of two of at most 8 (16 from 2^15 particles on) with at
  * least 128 sources each; an unsplit cluster in the

@@ -63,26 +63,94 @@ __device__ __forceinline__ double axpy(bool r32, double c, double y, double x) {
   return r32 ? (double)fmaf((float)c, (float)y, (float)x) : fma(c, y, x);
 }
 
+// Rows of one band of the symmetric path (SymRows in nb_internal.h) for one particle, and the running sums
+// of the bands before, in row order: thread q of Q (4 for clusters too small to fill the chip with one
+// thread per particle, else 1) takes rows q, q + Q, ....  Returns true after the cluster's last band, with
+// the particle's sums in the threads with q == 0 (all threads of the block must call it); else stores
+// the running sums.  HBM-bound (24 bytes per particle and row).
+template <int NC>
+__device__ __forceinline__ bool sum_rows(const Args& a, const DevCluster& c, int li, bool valid, int q, int Q, int band,
+                                         double (&sum)[NC], double (*sh)[4][64]) {
+  const SymRows rows = sym_rows(c.n, c.nseg, NC == 4, c.sym_doubles);
+  if (band < 0) band = rows.nbands - 1;
+  const int n = c.n, r0 = rows.row0(band), r1 = rows.row1(band);
+  double* const base = a.sym + c.part_off;
+  double* const run = base + ((size_t)rows.cap + q) * NC * n + li;  // running sums (more than one band)
+#pragma unroll
+  for (int d = 0; d < NC; ++d) sum[d] = band ? run[(size_t)d * n] : 0.0;
+  constexpr int kBatch = 8;  // rows in flight per thread
+  const int first = r0 + ((q - r0) & (Q - 1));
+  for (int r = first; r < r1; r += kBatch * Q) {
+    double v[kBatch][NC];
+#pragma unroll
+    for (int b = 0; b < kBatch; ++b)
+#pragma unroll
+      for (int d = 0; d < NC; ++d)
+        v[b][d] = r + b * Q < r1 ? base[((size_t)(r + b * Q - r0) * NC + d) * n + li] : 0.0;
+#pragma unroll
+    for (int b = 0; b < kBatch; ++b)
+      if (r + b * Q < r1)
+#pragma unroll
+        for (int d = 0; d < NC; ++d) sum[d] += v[b][d];
+  }
+  if (band < rows.nbands - 1) {
+    if (valid)
+#pragma unroll
+      for (int d = 0; d < NC; ++d) run[(size_t)d * n] = sum[d];
+    return false;
+  }
+  if (Q > 1) {
+    const int e = threadIdx.x & 63;
+#pragma unroll
+    for (int d = 0; d < NC; ++d) sh[d][q][e] = sum[d];
+    __syncthreads();
+    if (q == 0)
+#pragma unroll
+      for (int d = 0; d < NC; ++d)
+        for (int s = 1; s < Q; ++s) sum[d] += sh[d][s][e];
+  }
+  return true;
+}
+
 // Kick (v += kick_pre a) and drift (x += drift v) of one chunk (when `update`), and the chunk's
 // partial sums for its cluster's reference point ref = sum m x / sum m of the (new) positions,
-// mass-uniformity flag and bounding box (combined by k_reduce, or for small clusters by the pair
-// kernel: a kernel boundary rather than a device-scope fence orders the two, a fence would write back
-// the XCD's L2 in every block).  FINISH: a stage of an integrator step ends and the next begins; for
-// small clusters finished outside the pair kernel the pass first adds their j-ranges, stores the
-// acceleration and ends the stage with its kick, then starts the next stage.  One kernel and one trip
-// over the state in place of two (N = 1024, FP64: 8.2 us of combine and update in 4.6).
-// Launch-latency bound at the sizes where it matters.  Always launched before the pair kernels, whose
-// work counters it clears.
-template <bool FINISH>
+// mass-uniformity flag and bounding box (combined by k_reduce or chunk_frame: a kernel boundary rather
+// than a device-scope fence orders the two, a fence would write back the XCD's L2 in every block).
+// FINISH: a stage of an integrator step ends and the next begins; the pass first adds the pair sums of the
+// clusters that were not finished before it (symmetric: the last band's rows; small one-sided clusters:
+// their j-ranges), stores the acceleration and ends the stage with its kick, then starts the next
+// stage.  One kernel and one trip over the state in place of two (N = 1024, FP64: 8.2 us of combine and
+// update in 4.6; N = 7680: 10.0 in 6.3).  Block (x, y) takes chunk x, y = 0; with four threads per
+// particle (sum_rows), 64 of its particles.  Launch-latency bound at the sizes where it matters.
+// Always launched before the pair kernels, whose work counters it clears.
+// SYM: there may be symmetric clusters (without them N = 1024 takes 0.4 us less per step).
+template <bool FINISH, bool SYM>
 __global__ __launch_bounds__(kBlock) void k_update(Args a, int update) {
-  __shared__ double sh[6][kBlock];
-  if (blockIdx.x == 0)  // the pair kernels that follow start at item 0
+  __shared__ double sh[FINISH && SYM ? 3 : 1][4][64];
+  __shared__ double red[6][kBlock / 64];
+  if (blockIdx.x == 0 && blockIdx.y == 0)  // the pair kernels that follow start at item 0
     for (int q = threadIdx.x; q < a.ncounters; q += kBlock) a.item_counter[q] = 0;
   const Chunk ch = load_chunk(a);
   const DevCluster c = load_cluster(a, ch.cluster);
   const int t = threadIdx.x;
-  const bool valid = t < ch.count, r32 = a.prec == NB_FP32;
-  const long long i = c.off + ch.start + t;
+  const bool sym = FINISH && SYM && c.seg;
+  const int nrec = SYM ? chunk_records(c.n, c.seg) : 1, Q = sym ? sym_sums(c.n) : 1;
+  if (Q == 1 && blockIdx.y) return;
+  const int q = Q == 1 ? 0 : t >> 6, sub = Q == 1 ? t >> 6 : blockIdx.y;
+  const int e = 64 * sub + (t & 63);
+  const bool valid = e < ch.count, r32 = a.prec == NB_FP32;
+  const int li = ch.start + (valid ? e : 0);
+  long long i = c.off + li;
+  double g[3];
+  if (sym) {
+    sum_rows<3>(a, c, li, valid, q, Q, -1, g, sh);
+    if (q) return;
+    i = particle_index(a, c, li);
+    const double mc = a.mconst[ch.cluster];  // equal masses: the sums leave the mass out
+    if (mc != 0.0)
+#pragma unroll
+      for (int d = 0; d < 3; ++d) g[d] *= mc;
+  }
   double x[3] = {0.0, 0.0, 0.0}, m = 0.0, odd = 0.0;
   if (valid) {
     m = a.mass[i];
@@ -93,12 +161,16 @@ __global__ __launch_bounds__(kBlock) void k_update(Args a, int update) {
       const double* const cf = FINISH ? a.coef_next : a.coef;
       const double kc = cf ? cf[3 * ch.cluster] : FINISH ? a.pre_next : a.kick_pre;
       const double dc = cf ? cf[3 * ch.cluster + 1] : FINISH ? a.drift_next : a.drift;
-      double v[3], g[3];
+      double v[3];
 #pragma unroll
       for (int d = 0; d < 3; ++d) v[d] = a.vel[3 * i + d];
+      bool ends = sym;  // this pass ends the cluster's stage
       if (FINISH && small_cluster(c) && (c.split > 1 || (c.flags & kFlagDefer))) {
         double pt;
-        sum_ranges(a, c, ch.start + t, r32, g[0], g[1], g[2], pt);
+        sum_ranges(a, c, li, r32, g[0], g[1], g[2], pt);
+        ends = true;
+      }
+      if (ends) {
         finish_accel<true>(a, c, i, g[0], g[1], g[2], r32);
         const double kp = a.coef ? a.coef[3 * ch.cluster + 2] : a.kick_post;
         const bool kick = a.coef || kp != 0.0;
@@ -127,11 +199,16 @@ __global__ __launch_bounds__(kBlock) void k_update(Args a, int update) {
     mn[d] = valid ? x[d] : INFINITY;
     mx[d] = valid ? x[d] : -INFINITY;
   }
-  block_reduce<5>(val, sh);
-  if (!small_cluster(c)) block_minmax<3>(mn, mx, sh);  // small clusters are never sorted: no box
-  if (t == 0) {
-    double* p = a.partials + (size_t)blockIdx.x * kPartials;
-    for (int q = 0; q < 5; ++q) p[q] = val[q];
+  if (nrec > 1) {  // a record for each wave
+    wave_sum<5>(val);
+    if (c.nstiles) wave_minmax<3>(mn, mx);
+  } else {
+    block_reduce<5>(val, red);
+    if (c.nstiles) block_minmax<3>(mn, mx, red);  // only the sort wants the box
+  }
+  if ((nrec > 1 ? t & 63 : t) == 0) {
+    double* p = const_cast<double*>(partial_record(a, c, blockIdx.x - c.chunk0, nrec > 1 ? sub : 0));
+    for (int d = 0; d < 5; ++d) p[d] = val[d];
     for (int d = 0; d < 3; ++d) {
       p[5 + d] = mn[d];
       p[8 + d] = mx[d];
@@ -142,21 +219,23 @@ __global__ __launch_bounds__(kBlock) void k_update(Args a, int update) {
 // One block per cluster: combines the chunk partials in a fixed order into the reference point,
 // the common mass (mconst = the mass when all are equal, else 0) and the bounding box.
 __global__ __launch_bounds__(kBlock) void k_reduce(Args a) {
-  __shared__ double sh[6][kBlock];
+  __shared__ double sh[6][kBlock / 64];
   const DevCluster c = a.cl[blockIdx.x];
   const int t = threadIdx.x;
   double tot[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
   double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
   for (int q = t; q < c.nchunks; q += kBlock) {
-    const double* p = a.partials + (size_t)(c.chunk0 + q) * kPartials;
-    for (int r = 0; r < 5; ++r) tot[r] += p[r];
-    for (int d = 0; d < 3; ++d) {
-      lo[d] = fmin(lo[d], p[5 + d]);
-      hi[d] = fmax(hi[d], p[8 + d]);
-    }
+    for (int r = 0; r < 5; ++r) tot[r] += chunk_sum(a, c, q, r);
+    const double* p = partial_record(a, c, q, 0);
+    if (c.nstiles)
+      for (int w = 0; w < chunk_records(c.n, c.seg); ++w, p += kPartials)
+        for (int d = 0; d < 3; ++d) {
+          lo[d] = fmin(lo[d], p[5 + d]);
+          hi[d] = fmax(hi[d], p[8 + d]);
+        }
   }
   block_reduce<5>(tot, sh);
-  block_minmax<3>(lo, hi, sh);
+  if (c.nstiles) block_minmax<3>(lo, hi, sh);
   if (t == 0) {
     const double M = tot[3];
     a.ref[blockIdx.x] = M > 0.0 ? make_double4(tot[0] / M, tot[1] / M, tot[2] / M, M)
@@ -177,7 +256,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce(Args a) {
 // non-finite flag.
 __global__ __launch_bounds__(kBlock) void k_energy(Args a) {
   constexpr int NS = kEnergySums;
-  __shared__ double sh[NS][kBlock];
+  __shared__ double sh[NS][kBlock / 64];
   const Chunk ch = load_chunk(a);
   const DevCluster c = load_cluster(a, ch.cluster);
   const int t = threadIdx.x;
@@ -261,61 +340,21 @@ __device__ __forceinline__ void combine_split(const Args& a, const Chunk& ch, co
   if (potmode && a.pot) a.pot[gi] = r32 ? (double)(-(float)a.G * (float)pt) : -a.G * pt;
 }
 
-// One band of the symmetric path (SymRows in nb_internal.h): every particle's rows of the band, and
-// the running sums of the bands before, in row order; after the last band the particle is finished.
-// HBM-bound (24 bytes per particle and row).  Q = 4 threads per particle, each taking every fourth
-// row, for clusters too small to fill the chip with one: block (x, y) then takes 64 particles of chunk
-// x, wave q the rows q, q + 4, ...; else block (x, 0) takes the chunk, one thread per particle.
+// One band of the symmetric path; after a cluster's last band the particle is finished.  Block (x, y) as in
+// k_update.
 template <int NC>
 __device__ __forceinline__ void combine_sym(const Args& a, const Chunk& ch, const DevCluster& c, int band, int kick,
                                             double (*sh)[4][64]) {
-  const SymRows rows = sym_rows(c.n, c.nseg, NC == 4, c.sym_doubles);
-  if (band >= rows.nbands) return;
-  const int Q = sym_sums(c.n);
+  if (band < 0 || band >= sym_rows(c.n, c.nseg, NC == 4, c.sym_doubles).nbands) return;
+  const int Q = sym_sums(c.n), t = threadIdx.x;
   if (Q == 1 && blockIdx.y) return;
-  const int t = threadIdx.x, q = Q == 1 ? 0 : t >> 6;
-  const int e = Q == 1 ? t : 64 * blockIdx.y + (t & 63);
+  const int q = Q == 1 ? 0 : t >> 6, e = Q == 1 ? t : 64 * blockIdx.y + (t & 63);
   const bool valid = e < ch.count;
-  const int li = ch.start + (valid ? e : 0), n = c.n;
-  const int r0 = rows.row0(band), r1 = rows.row1(band);
-  const bool last = band == rows.nbands - 1;
-  double* const base = a.sym + c.part_off;
-  double* const run = base + ((size_t)rows.cap + q) * NC * n + li;  // running sums (more than one band)
+  const int li = ch.start + (valid ? e : 0);
   double sum[NC];
-#pragma unroll
-  for (int d = 0; d < NC; ++d) sum[d] = band ? run[(size_t)d * n] : 0.0;
-  constexpr int kBatch = 8;  // rows in flight per thread
-  const int first = r0 + ((q - r0) & (Q - 1));
-  for (int r = first; r < r1; r += kBatch * Q) {
-    double v[kBatch][NC];
-#pragma unroll
-    for (int b = 0; b < kBatch; ++b)
-#pragma unroll
-      for (int d = 0; d < NC; ++d)
-        v[b][d] = r + b * Q < r1 ? base[((size_t)(r + b * Q - r0) * NC + d) * n + li] : 0.0;
-#pragma unroll
-    for (int b = 0; b < kBatch; ++b)
-      if (r + b * Q < r1)
-#pragma unroll
-        for (int d = 0; d < NC; ++d) sum[d] += v[b][d];
-  }
-  if (!last) {
-    if (valid)
-#pragma unroll
-      for (int d = 0; d < NC; ++d) run[(size_t)d * n] = sum[d];
-    return;
-  }
-  if (Q > 1) {
-#pragma unroll
-    for (int d = 0; d < NC; ++d) sh[d][q][t & 63] = sum[d];
-    __syncthreads();
-    if (q) return;
-#pragma unroll
-    for (int d = 0; d < NC; ++d)
-      for (int s = 1; s < Q; ++s) sum[d] += sh[d][s][t];
-  }
+  if (!sum_rows<NC>(a, c, li, valid, q, Q, band, sum, sh) || q) return;
   if (!valid) return;
-  const double mc = a.mconst[ch.cluster];  // equal masses: the sums leave the mass out
+  const double mc = a.mconst[ch.cluster];
   if (mc != 0.0)
 #pragma unroll
     for (int d = 0; d < NC; ++d) sum[d] *= mc;
@@ -348,10 +387,12 @@ hipError_t launch_combine(const Args& a, int band, bool potmode, bool kick, Comb
 }
 
 hipError_t launch_update(const Args& a, bool update, bool finish, hipStream_t s) {
-  if (finish)
-    hipLaunchKernelGGL(k_update<true>, dim3(a.nchunks), dim3(kBlock), 0, s, a, 1);
+  if (!finish)
+    hipLaunchKernelGGL((k_update<false, true>), dim3(a.nchunks), dim3(kBlock), 0, s, a, update ? 1 : 0);
+  else if (a.sym)
+    hipLaunchKernelGGL((k_update<true, true>), dim3(a.nchunks, 4), dim3(kBlock), 0, s, a, 1);
   else
-    hipLaunchKernelGGL(k_update<false>, dim3(a.nchunks), dim3(kBlock), 0, s, a, update ? 1 : 0);
+    hipLaunchKernelGGL((k_update<true, false>), dim3(a.nchunks), dim3(kBlock), 0, s, a, 1);
   return hipGetLastError();
 }
 

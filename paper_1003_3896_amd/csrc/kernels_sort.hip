@@ -173,7 +173,7 @@ __global__ __launch_bounds__(kBlock) void k_rscatter(Args a, int src, int shift)
 // symmetric path, whose i-groups are the chunks, the frame of each group: the centre of its box and
 // (3/4 of the box diagonal)^2 with the margin of k_farflags.
 __global__ __launch_bounds__(kBlock) void k_gather(Args a) {
-  __shared__ double sh[6][kBlock];
+  __shared__ double sh[6][kBlock / 64];
   const Chunk ch = load_chunk(a);
   const DevCluster c = load_cluster(a, ch.cluster);
   const int t = threadIdx.x;

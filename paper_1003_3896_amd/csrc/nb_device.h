@@ -4,15 +4,29 @@
 
 namespace nb {
 
-// Fixed-order reduction of V doubles per thread over the block (a shuffle tree inside each wave,
-// then the waves in order); result valid in thread 0.  sh needs [V][kBlock / 64].
+// Fixed-order reductions of V doubles per thread: a shuffle tree inside each wave (valid in its lane 0),
+// then over the block the waves in order (valid in thread 0).  sh needs [V] (minima and maxima: [2 V]).
 template <int V>
-__device__ __forceinline__ void block_reduce(double (&val)[V], double (*sh)[kBlock]) {
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+__device__ __forceinline__ void wave_sum(double (&val)[V]) {
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1)
 #pragma unroll
     for (int q = 0; q < V; ++q) val[q] += __shfl_down(val[q], m);
+}
+template <int V>
+__device__ __forceinline__ void wave_minmax(double (&mn)[V], double (&mx)[V]) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1)
+#pragma unroll
+    for (int q = 0; q < V; ++q) {
+      mn[q] = fmin(mn[q], __shfl_down(mn[q], m));
+      mx[q] = fmax(mx[q], __shfl_down(mx[q], m));
+    }
+}
+template <int V>
+__device__ __forceinline__ void block_reduce(double (&val)[V], double (*sh)[kBlock / 64]) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  wave_sum<V>(val);
   __syncthreads();  // sh is free (a previous reduction has been read)
   if (lane == 0)
 #pragma unroll
@@ -26,18 +40,10 @@ __device__ __forceinline__ void block_reduce(double (&val)[V], double (*sh)[kBlo
       val[q] = s;
     }
 }
-
-// Minima and maxima of V values per thread over the block; result valid in thread 0.
 template <int V>
-__device__ __forceinline__ void block_minmax(double (&mn)[V], double (&mx)[V], double (*sh)[kBlock]) {
+__device__ __forceinline__ void block_minmax(double (&mn)[V], double (&mx)[V], double (*sh)[kBlock / 64]) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1)
-#pragma unroll
-    for (int q = 0; q < V; ++q) {
-      mn[q] = fmin(mn[q], __shfl_down(mn[q], m));
-      mx[q] = fmax(mx[q], __shfl_down(mx[q], m));
-    }
+  wave_minmax<V>(mn, mx);
   __syncthreads();
   if (lane == 0)
 #pragma unroll
@@ -157,25 +163,38 @@ __device__ __forceinline__ double4 record64(const Args& a, long long gi) {
   return make_double4(a.pos[3 * gi], a.pos[3 * gi + 1], a.pos[3 * gi + 2], a.mass[gi]);
 }
 
-// Reference point (centre of mass) and common mass of a small cluster, from its chunk partials (laid out
-// as k_update writes them): every wave reduces them by itself, which costs an item well under a
-// microsecond where a kernel of its own between the update and the pair kernel cost 3.3.
+// A partial record of a chunk (or of 64 particles, chunk_records): sums m x, m y, m z, m, count of masses !=
+// the cluster's first; then min x, y, z and max x, y, z.
 constexpr int kPartials = 11;
+__device__ __forceinline__ const double* partial_record(const Args& a, const DevCluster& c, int chunk, int sub) {
+  return a.partials + ((size_t)c.rec0 + (size_t)chunk * chunk_records(c.n, c.seg) + sub) * kPartials;
+}
+// Sum q of the cluster's chunk, its records in order.
+__device__ __forceinline__ double chunk_sum(const Args& a, const DevCluster& c, int chunk, int q) {
+  const double* p = partial_record(a, c, chunk, 0) + q;
+  double s = p[0];
+  for (int w = 1; w < chunk_records(c.n, c.seg); ++w) s += p[w * kPartials];
+  return s;
+}
+
+// Reference point (centre of mass) and common mass of a small cluster, by each wave that needs them: without
+// the launch of k_reduce, which cost more (3.3 us per evaluation) than the microsecond that this takes at the
+// start of an item.  (The symmetric kernel has more items and chunks: there it cost N = 15360 7 us to
+// save 5, and the 512-cluster ensemble 5%.)  Called by whole waves; the point is valid in lane 0.
 template <bool CENTRE>
 __device__ __forceinline__ double4 chunk_frame(const Args& a, const DevCluster& c, double& mc) {
-  static_assert(kSmallChunks <= 64, "one partial per lane");
   const int lane = threadIdx.x & 63;
   const bool has = lane < c.nchunks;
-  const double* p = a.partials + (size_t)(c.chunk0 + (has ? lane : 0)) * kPartials;
+  const double* p = partial_record(a, c, has ? lane : 0, 0);
   mc = __any(has && p[4] != 0.0) ? 0.0 : a.mass[c.off];
   if (!CENTRE) return make_double4(0.0, 0.0, 0.0, 0.0);
   double v[4];
 #pragma unroll
   for (int d = 0; d < 4; ++d) v[d] = has ? p[d] : 0.0;
 #pragma unroll
-  for (int s = kSmallChunks / 2; s >= 1; s >>= 1)
+  for (int s = kSymMin / kChunk / 2; s >= 1; s >>= 1)
 #pragma unroll
-    for (int d = 0; d < 4; ++d) v[d] += __shfl_xor(v[d], s);
+    for (int d = 0; d < 4; ++d) v[d] += __shfl_down(v[d], s);
   return v[3] > 0.0 ? make_double4(v[0] / v[3], v[1] / v[3], v[2] / v[3], v[3]) : make_double4(0.0, 0.0, 0.0, 0.0);
 }
 

@@ -39,7 +39,8 @@ struct DevCluster {
   int tbox0;           // first j-tile box of the cluster (NB_FP32DL; room for split x ceil(jlen/128))
   int seg;             // symmetric path: particles per segment (0: the cluster takes the one-sided path)
   int nseg;            // symmetric path: segments
-  int pad0[2];
+  int rec0;            // first partial record of the cluster (chunk_records per chunk)
+  int pad0;
   long long sym_doubles;  // symmetric path: room for its rows (doubles)
 };
 constexpr int kFlagField = 1;     // add the galaxy field
@@ -74,12 +75,17 @@ constexpr int kSymBlocksPerCu = 2;  // of 8 waves: 4 per SIMD, an even number (p
 // Particles per segment, a function of the cluster's size alone (its sums, and so its bits, depend on
 // it): small enough that one cluster has a few items per CU, large enough that the rows (48 bytes
 // written and read per particle and segment) stay a small part of the time (the combine pass took 8%
-// of the 512-cluster ensemble's step with 256 up to 16383, 4% with 512 from 8192 on).  The block's
-// waves cover a segment with their i-groups: 2 x 128, 2 x 256 or 4 x 256.
-__host__ __device__ inline int sym_segment(int n) { return n < 8192 ? 256 : n < 65536 ? 512 : 1024; }
+// of the 512-cluster ensemble's step with 256 up to 16383, 4% with 512 from 8192 on; N = 65536: 8.04 ms
+// per sym6 step with 1024, 7.65 with 512).  The block's waves cover a segment with their i-groups: 2 x
+// 128, 2 x 256 or 4 x 256.
+__host__ __device__ inline int sym_segment(int n) { return n < 8192 ? 256 : n < 131072 ? 512 : 1024; }
 // Running sums the combine pass keeps per particle between bands (also its threads per particle): four
 // while there are too few particles to fill the chip with one thread each.
 __host__ __device__ inline int sym_sums(int n) { return n < 131072 ? 4 : 1; }
+
+// Partial records per chunk: the combine pass of a symmetric cluster with four threads per particle takes 64
+// particles per block.
+__host__ __device__ inline int chunk_records(int n, int seg) { return seg && sym_sums(n) == 4 ? 4 : 1; }
 
 // Rows of the partial-sum table.  Segment pairs are ordered by their circular distance delta = 0 ..
 // nseg / 2: the item (A, A + delta) writes row 2 delta - 1 of A's particles and row 2 delta of the
@@ -160,8 +166,7 @@ struct Args {
   int nitems;
   int* item_counter;   // dynamic work distribution of the persistent pair kernel
   int* chunk_counter;  // [B] chunks finished per cluster (last-block reductions)
-  double* partials;    // [nchunks][11] chunk sums m x, m y, m z, m, count of masses != the cluster's
-                       // first; then min x, y, z and max x, y, z
+  double* partials;    // records of kPartials doubles (nb_device.h)
   double* box;         // [B][6] bounding box of each cluster (min xyz, max xyz)
   // Hilbert-curve sort (NB_FP32DL): keys and local indices (double-buffered), per-tile digit counts and
   // offsets, and the result: perm[off + l] = local index of the particle at sorted position l
@@ -213,8 +218,9 @@ struct TileCfg {
 };
 
 // Launchers (kernels_*.hip).  All return hipSuccess or the launch error.
-// kick + drift (when update) and chunk partials; `finish`: the small clusters' sums first (small_cluster),
-// with the kick that ends their stage, then the next stage's kick and drift
+// kick + drift (when update) and chunk partials; `finish`: first the last band of the symmetric clusters'
+// rows and the small clusters' ranges (small_cluster), with the kick that ends their stage, then the next
+// stage's kick and drift
 hipError_t launch_update(const Args& a, bool update, bool finish, hipStream_t s);
 // reference point, common mass and box of every cluster from the chunk partials
 hipError_t launch_reduce(const Args& a, int B, hipStream_t s);
@@ -222,7 +228,7 @@ hipError_t launch_reduce(const Args& a, int B, hipStream_t s);
 hipError_t launch_pair(const Args& a, const TileCfg& t, int grid, bool mask, bool potmode, bool kick,
                        hipStream_t s);
 hipError_t launch_energy(const Args& a, hipStream_t s);
-// one band of the symmetric path, and the sums of the one-sided clusters named
+// one band of the symmetric path (-1: none), and the sums of the one-sided clusters named
 enum CombineOneSided { kCombineNone, kCombineLarge, kCombineAll };
 hipError_t launch_combine(const Args& a, int band, bool potmode, bool kick, CombineOneSided which, hipStream_t s);
 hipError_t launch_pair_sym(const Args& a, const SymBand& b, int grid, bool mask, bool potmode, hipStream_t s);
@@ -258,9 +264,9 @@ __device__ __forceinline__ long long particle_index(const Args& a, const DevClus
   return c.off + (a.perm && c.nstiles ? a.perm[c.off + l] : l);
 }
 
-// Clusters of the one-sided path below the symmetric one: never sorted, at most kSmallChunks chunks, whose
-// partials the pair kernel reduces by itself (chunk_frame).
-constexpr int kSmallChunks = kSymMin / kChunk;
+// Clusters of the one-sided path below the symmetric one: never sorted, few enough chunks for the pair
+// kernel to reduce their partials by itself (chunk_frame).
+static_assert(kSymMin / kChunk <= 64, "one chunk per lane");
 __host__ __device__ inline bool small_cluster(const DevCluster& c) { return c.n < kSymMin; }
 
 }  // namespace nb

@@ -110,6 +110,8 @@ __device__ __forceinline__ DevCluster uniform_cluster(const Args& a, int b) {
   u.jlen = wave_uniform(c.jlen);
   u.stile0 = wave_uniform(c.stile0);
   u.nstiles = wave_uniform(c.nstiles);
+  u.seg = 0;  // one-sided
+  u.rec0 = wave_uniform(c.rec0);
   return u;
 }
 

@@ -30,10 +30,10 @@
 // Why 8 waves to an item and 2 blocks per CU: SIMDs serve their oldest waves first, so when the items
 // run out every CU still holds all its blocks' items, half done on average; fewer, faster items per CU
 // shorten that tail (N = 65536 in NB_FP32DL 1.22 -> 1.10 ms against 4 blocks of 4 waves, N = 15360 in
-// NB_FP32DS 101 -> 88 us).  Two blocks per CU of 4 waves (2 waves per SIMD) were 11 to 18% slower.
-// Against the one-sided kernels: N = 262144 in NB_FP32DL 17.0 -> 13.1 ms, N = 65536 1.25 -> 1.0 ms,
-// N = 15360 in NB_FP32DS 140 -> 88 us, N = 65536 in FP64 with the potential 3.0 -> 2.2 ms, 512 clusters
-// of 256..16384 in NB_FP32DS 5.6 -> 4.1 ms.
+// NB_FP32DS 101 -> 88 us; with segments of 512 instead of 1024 particles at 65536, 0.97 ms).  Two blocks per CU of 4 waves (2 waves per SIMD) were 11 to 18% slower.
+// Against the one-sided kernels: N = 262144 in NB_FP32DL 17.0 -> 12.8 ms, N = 65536 1.25 -> 0.95 ms,
+// N = 15360 in NB_FP32DS 140 -> 88 us, N = 65536 in FP64 with the potential 3.0 -> 2.1 ms, 512 clusters
+// of 256..16384 in NB_FP32DS 5.6 -> 4.2 ms.
 #pragma once
 #include "nb_device.h"
 #include <type_traits>
@@ -42,7 +42,11 @@ namespace nb {
 
 constexpr int kSymBlock = 512;            // threads: 8 waves
 constexpr int kSymWaves = kSymBlock / 64;
-constexpr int kSymAcc = 512;              // LDS accumulators of one block (groups x chunk)
+// LDS accumulators of one block (groups x chunk): 1024 (half the flushes, each two barriers) against 512 made
+// the N = 15360 to 262144 steps 0.5 to 1.5% faster; with the potential they would not fit beside the staged
+// strips.
+template <bool POT>
+constexpr int kSymAcc = POT ? 512 : 1024;
 
 // v_rsq_f32 between two s_nop (see the top of the file; the second one is also the wait state its
 // consumer needs).
@@ -244,9 +248,9 @@ __device__ __forceinline__ void sym_strip(const SymStage<FAM>& st, SymLane<R, K>
     if constexpr (SYM) {
       double* a = acc + 16 * c + l16;
       lds_add(a, (double)bx);
-      lds_add(a + kSymAcc, (double)by);
-      lds_add(a + 2 * kSymAcc, (double)bz);
-      if constexpr (POT) lds_add(a + 3 * kSymAcc, (double)bp);
+      lds_add(a + kSymAcc<POT>, (double)by);
+      lds_add(a + 2 * kSymAcc<POT>, (double)bz);
+      if constexpr (POT) lds_add(a + 3 * kSymAcc<POT>, (double)bp);
     }
     if constexpr (FAM != FAM_F64) {
       if (p & 1) sym_fold<POT, K>(v, A);
@@ -361,10 +365,10 @@ template <int FAM, bool MASK, bool POT, int K>
 __global__ __launch_bounds__(kSymBlock, 4) void k_pair_sym(Args a, SymBand band) {
   using R = typename std::conditional<FAM == FAM_F64, double, float>::type;
   constexpr bool SORTED = FAM == FAM_DL, DS = FAM == FAM_DS || FAM == FAM_DL;
-  constexpr int NC = POT ? 4 : 3, G = 64 * K;
+  constexpr int NC = POT ? 4 : 3, G = 64 * K, ACC = kSymAcc<POT>;
   struct Work {
     SymStage<FAM> st[kSymWaves];
-    double acc[NC * kSymAcc];
+    double acc[NC * ACC];
   };
   constexpr size_t kReduce = sizeof(double) * NC * G * 6;  // sums of the waves with gj > 0
   __shared__ __align__(16) char lds[sizeof(Work) > kReduce ? sizeof(Work) : kReduce];
@@ -372,7 +376,7 @@ __global__ __launch_bounds__(kSymBlock, 4) void k_pair_sym(Args a, SymBand band)
   Work& sh = *reinterpret_cast<Work*>(lds);
   const int tid = threadIdx.x, wave = uniform(tid >> 6), lane = tid & 63;
   SymStage<FAM>& st = sh.st[wave];
-  for (int e = tid; e < NC * kSymAcc; e += kSymBlock) sh.acc[e] = 0.0;
+  for (int e = tid; e < NC * ACC; e += kSymBlock) sh.acc[e] = 0.0;
   __syncthreads();
   for (int it = blockIdx.x; it < band.nitems;) {
     // a wave that is not in the pair loops (set-up, sums, stores) goes before those that are: its
@@ -394,16 +398,16 @@ __global__ __launch_bounds__(kSymBlock, 4) void k_pair_sym(Args a, SymBand band)
     const int ib = A * S, ie = min(n, ib + S), jb = B * S, je = min(n, jb + S);
     const int GI = S >= 4 * G ? 4 : 2, GJ = kSymWaves / GI;
     const int gi = wave / GJ, gj = wave - gi * GJ;
-    const int CH = kSymAcc / GI;  // j-particles between two flushes
+    const int CH = ACC / GI;  // j-particles between two flushes
     const bool eq = scalar(a.mconst)[ci] != 0.0;
     const R e2 = FAM == FAM_F64 ? (R)c->eps2 : (R)c->eps2f;
-    const ScalarPtr<double> frame =
-        scalar(reinterpret_cast<const double*>(FAM == FAM_DL ? a.gbox + c->chunk0 : a.ref + ci));
     const bool absolute = a.prec == 0;
     double* const acc = sh.acc + gi * CH;
     const int wb = ib + gi * G;  // this wave's group (the block's cover the segment)
     const bool active = wb < ie;
-    const ScalarPtr<double> f = frame + (FAM == FAM_DL ? 4 * (min(wb, n - 1) / kChunk) : 0);
+    // the frame: the cluster's centre of mass, in the local mode the box of the group's chunk
+    const ScalarPtr<double> f = scalar(reinterpret_cast<const double*>(
+        FAM == FAM_DL ? a.gbox + c->chunk0 + min(wb, n - 1) / kChunk : a.ref + ci));
     const double4 ref = make_double4(f[0], f[1], f[2], f[3]);
     SymRaw raw = sym_fetch<SORTED>(a, off + jb + 64 * gj + lane, jb + 64 * gj + lane < je);
     SymLane<R, K> v;
@@ -473,7 +477,7 @@ __global__ __launch_bounds__(kSymBlock, 4) void k_pair_sym(Args a, SymBand band)
           for (int q = 0; q < NC; ++q) {
             double t = 0.0;
             for (int g = 0; g < GI; ++g) {
-              double* const e = sh.acc + q * kSymAcc + g * CH + tid;
+              double* const e = sh.acc + q * ACC + g * CH + tid;
               t += *e;
               *e = 0.0;
             }
@@ -530,7 +534,7 @@ __global__ __launch_bounds__(kSymBlock, 4) void k_pair_sym(Args a, SymBand band)
       }
     }
     __syncthreads();
-    for (int e = tid; e < NC * kSymAcc; e += kSymBlock) sh.acc[e] = 0.0;  // the sums may have lain over them
+    for (int e = tid; e < NC * ACC; e += kSymBlock) sh.acc[e] = 0.0;  // the sums may have lain over them
     if (tid == 0) s_item = next;
     __syncthreads();
     it = uniform(s_item);

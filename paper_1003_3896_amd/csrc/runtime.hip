@@ -90,7 +90,7 @@ struct Plan {
   int ntboxes = 0;  // j-tile box slots (NB_FP32DL only)
   bool anymask = false;
   bool anysplit = false;  // some one-sided cluster is finished by the combine pass (split, or kFlagDefer)
-  bool anylarge = false;  // some cluster is not small (small_cluster): it needs k_reduce, and its own combine
+  bool reduce = false;    // some cluster needs k_reduce (is not small)
   int maxn_small = 0, maxn_large = 0;  // largest one-sided cluster below and above the symmetric path
   std::vector<int> sym;   // clusters on the symmetric path, largest first
   int ndelta = 0;         // segment distances of the largest of them (bounds its bands)
@@ -129,15 +129,16 @@ int split_of(int n) {
   return s;
 }
 
-// Room for the rows of the symmetric path: at most 64 rows per particle at a time (beside the running
-// sums), and at most the rows that leave a cluster of 2^18 particles inside the static scratch of the
-// no-allocation entry point; at least two rows per band, with the potential.
-constexpr int kSymRowsMax = 64;
-constexpr long long kSymBudget = 3LL * 34 << 18;  // doubles per cluster
+// Room for the rows of the symmetric path: all of them, with the potential, up to 105 segments (3 of its 4
+// sums up to 140); beyond, 34 rows of clusters of 2^18 particles and more, and as many bytes (204 MiB,
+// which leaves 2^18 particles inside the static scratch of the no-allocation entry point) for smaller
+// ones; at least two rows per band, with the potential.  More room means fewer bands, and at the end of
+// each the chip runs empty (N = 983040 with 8 rows: 7% slower than with 33).
+constexpr int kSymRowsMax = 140;
 long long sym_doubles_min(int n) { return 4LL * n * (sym_sums(n) + 2); }
 long long sym_doubles_want(int n, int nseg) {
-  const long long rows = nseg <= kSymRowsMax ? nseg : kSymRowsMax + sym_sums(n);
-  return std::max(sym_doubles_min(n), std::min(3 * rows * n, kSymBudget));
+  const long long most = 3LL * 34 * std::max(n, 1 << 18);
+  return std::max(sym_doubles_min(n), std::min({4LL * nseg * n, 3LL * kSymRowsMax * n, most}));
 }
 
 // far-tile words of one item's j-range: two bits per tile, 16 tiles per word
@@ -244,6 +245,7 @@ struct Counts {
   int B = 0, nchunks = 0, nstiles = 0;
   long long ntot = 0;
   long long nitems = 0, npart = 0, nflagwords = 0, ntiles = 0;  // one-sided path
+  long long nrecords = 0;                                       // partial records of the chunks
   long long nsymtab = 0, nbands = 0, symdoubles = 0;            // symmetric path (table entries, most bands)
 };
 
@@ -274,7 +276,7 @@ Layout make_layout(const Counts& m) {
   L.box = o;
   o = align_up(o + sizeof(double) * 6 * B);
   L.partials = o;
-  o = align_up(o + sizeof(double) * 11 * nchunks);
+  o = align_up(o + sizeof(double) * 11 * (size_t)m.nrecords);
   L.epart = o;
   o = align_up(o + sizeof(double) * kEnergySums * nchunks);
   L.pot = o;
@@ -320,7 +322,7 @@ int build_plan(const nbody_system* sys, Plan& p, size_t limit = 0) {
   p.ndelta = 0;
   const bool sorted = sys->prec == NB_FP32DL;
   p.anymask = false;
-  p.anysplit = p.anylarge = false;
+  p.anysplit = p.reduce = false;
   p.maxn_small = p.maxn_large = 0;
   Counts m, one;  // one: every cluster on the one-sided path
   long long want = 0, least = 0;
@@ -373,7 +375,9 @@ int build_plan(const nbody_system* sys, Plan& p, size_t limit = 0) {
       p.anysplit |= via_combine;
       (small_cluster(c) ? p.maxn_small : p.maxn_large) = std::max(small_cluster(c) ? p.maxn_small : p.maxn_large, c.n);
     }
-    p.anylarge |= !small_cluster(c);
+    p.reduce |= !small_cluster(c);
+    c.rec0 = (int)m.nrecords;
+    m.nrecords += (long long)c.nchunks * chunk_records(c.n, c.seg);
     if (sorted) m.nstiles += (c.n + kSortTile - 1) / kSortTile;
     c.stile0 = (int)p.stiles.size();
     c.nstiles = 0;
@@ -391,6 +395,7 @@ int build_plan(const nbody_system* sys, Plan& p, size_t limit = 0) {
   m.B = one.B = p.B;
   m.ntot = one.ntot = p.ntot;
   m.nchunks = one.nchunks = p.nchunks;
+  one.nrecords = p.nchunks;
   one.nstiles = m.nstiles;
   m.nbands = 2 * p.ndelta;
   const Layout l1 = make_layout(one);
@@ -652,10 +657,11 @@ int pair_launch(nbody_ctx* ctx, const Prepared& P, const OneSided& o, int counte
   return NB_OK;
 }
 
-// The last (or only) combine pass of an evaluation.
-int combine(const Prepared& P, bool potmode, bool kick, bool small, hipStream_t s) {
-  const hipError_t e = launch_combine(P.a, P.bands.empty() ? 0 : P.bands.back().index, potmode, kick,
-                                      small ? kCombineAll : kCombineLarge, s);
+// The last (or only) combine pass of an evaluation; all = false: for the clusters that the fused pass
+// between two stages leaves out.
+int combine(const Prepared& P, bool potmode, bool kick, bool all, hipStream_t s) {
+  const hipError_t e = launch_combine(P.a, all && !P.bands.empty() ? P.bands.back().index : -1, potmode, kick,
+                                      all ? kCombineAll : kCombineLarge, s);
   if (e != hipSuccess) return fail(NB_ERR_HIP, "combine kernel launch: %s", hipGetErrorString(e));
   return NB_OK;
 }
@@ -663,11 +669,13 @@ int combine(const Prepared& P, bool potmode, bool kick, bool small, hipStream_t 
 // The pair sums of the positions that an update pass has just left (and reduced to chunk partials):
 // [reference points -> sort] -> pair kernels of the one-sided and of the symmetric clusters, the latter
 // with a combine pass after every band but the last.  Per-kernel timing spans the pair kernels.
-int pair_pass(nbody_ctx* ctx, Prepared& P, bool potmode, bool kick, hipStream_t s) {
+// `again`: masses and system are those of the evaluation before in the same call, so the modes that need
+// neither reference points nor boxes keep its common masses and skip the reduction (4 us).
+int pair_pass(nbody_ctx* ctx, Prepared& P, bool potmode, bool kick, bool again, hipStream_t s) {
   hipError_t e;
   const Plan& p = ctx->plan;
   int rc;
-  if (p.anylarge && (e = launch_reduce(P.a, p.B, s)) != hipSuccess)
+  if (p.reduce && (P.centred || !again) && (e = launch_reduce(P.a, p.B, s)) != hipSuccess)
     return fail(NB_ERR_HIP, "reduce kernel launch: %s", hipGetErrorString(e));
   if (P.a.nstiles) {
     e = launch_sort(P.a, p.B, s);  // also the work items' boxes and far-tile bits
@@ -702,14 +710,14 @@ int pair_pass(nbody_ctx* ctx, Prepared& P, bool potmode, bool kick, hipStream_t 
 int evaluate(nbody_ctx* ctx, Prepared& P, bool potmode, hipStream_t s) {
   hipError_t e = launch_update(P.a, false, false, s);  // also clears the pair kernels' work counters
   if (e != hipSuccess) return fail(NB_ERR_HIP, "update kernel launch: %s", hipGetErrorString(e));
-  int rc = pair_pass(ctx, P, potmode, false, s);
+  int rc = pair_pass(ctx, P, potmode, false, false, s);
   if (rc || (P.bands.empty() && !ctx->plan.anysplit)) return rc;
   return combine(P, potmode, false, true, s);
 }
 
 // `stages` consecutive integrator stages (set_stage(k) sets the coefficients of stage k in P.a): each is
-// kick + drift, an evaluation and a kick.  Between two stages one pass ends the first for the small
-// clusters and starts the second; the others are finished by a combine pass before it.
+// kick + drift, an evaluation and a kick.  Between two stages one pass ends the first and starts the
+// second (clusters above the symmetric path are finished by a combine pass before it).
 template <class F>
 int run_stages(nbody_ctx* ctx, Prepared& P, int stages, F& set_stage, hipStream_t s) {
   hipError_t e;
@@ -728,8 +736,8 @@ int run_stages(nbody_ctx* ctx, Prepared& P, int stages, F& set_stage, hipStream_
     }
     set_stage(k);
     const bool kick = P.a.coef != nullptr || P.a.kick_post != 0.0;
-    if ((rc = pair_pass(ctx, P, false, kick, s))) return rc;
-    if (combined && (last || ctx->plan.anylarge) && (rc = combine(P, false, kick, last, s))) return rc;
+    if ((rc = pair_pass(ctx, P, false, kick, k > 0, s))) return rc;
+    if ((last ? combined : ctx->plan.maxn_large > 0) && (rc = combine(P, false, kick, last, s))) return rc;
     if (last) return NB_OK;
     e = launch_update(P.a, true, true, s);
     if (e != hipSuccess) return fail(NB_ERR_HIP, "update kernel launch: %s", hipGetErrorString(e));
@@ -1020,6 +1028,7 @@ size_t nbody_workspace_bytes_max(int64_t max_particles, int32_t max_clusters) {
   m.B = (int)B;
   m.ntot = n;
   m.nchunks = (int)(B + n / kChunk);
+  m.nrecords = B + 4 * (n / kChunk);  // a cluster with four records per chunk has at least 16 chunks
   m.nitems = kMaxSplit * (B + n / 64);
   m.npart = std::min(kMaxSplit * n, B * (long long)NB_SPLIT_CAP + n);
   m.nstiles = (int)(B + n / kSortTile);  // the sort of NB_FP32DL
@@ -1029,12 +1038,12 @@ size_t nbody_workspace_bytes_max(int64_t max_particles, int32_t max_clusters) {
   // j-tile boxes: sum over clusters of split_c ceil(jlen_c/128) <= n/128 + 17 B
   m.ntiles = n / 128 + (kMaxSplit + 1) * B;
   if (n >= kSymMin) {
-    // distances of a cluster: ceil(n_c / seg_c) / 2 + 1 <= n_c/512 + 2; room: at most kSymRowsMax + 4 rows
-    // of 3 doubles per particle, and at most the budget per cluster
+    // distances of a cluster: ceil(n_c / seg_c) / 2 + 1 <= n_c/512 + 2; room: at most kSymRowsMax rows of 3
+    // doubles per particle
     const long long bs = std::min(B, n / kSymMin);  // clusters that can be on the symmetric path
     m.nbands = 2 * (n / 512 + 2);
     m.nsymtab = n / 512 + 2 * bs;
-    m.symdoubles = std::min(3 * (kSymRowsMax + 4) * n, bs * kSymBudget);
+    m.symdoubles = 3 * kSymRowsMax * n;
   }
   return make_layout(m).total;
 }

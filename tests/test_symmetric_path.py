@@ -1,5 +1,5 @@
 """The symmetric pair path (clusters of 4096 to 2^20 particles): each unordered pair evaluated once, both
-accelerations kept.  Sizes at the edges of its segments (256 below 8192 particles, 512 below 65536,
+accelerations kept.  Sizes at the edges of its segments (256 below 8192 particles, 512 below 131072,
 1024 from there), with remainders of one particle, odd and even numbers of segments, several bands of
 partial-sum rows, equal and unequal masses, eps = 0, batches that mix it with the one-sided path;
 against the oracle with the gates of gpu_helpers (derived there), and bitwise where only the room for
