@@ -236,12 +236,14 @@ __device__ __forceinline__ void sym_fold(SymLane<float, K>& v, SymSums<K>& A) {
 // The lane's K i-particles against one staged strip.  acc: the wave group's LDS accumulators of the
 // strip's 64 j-particles (only this wave adds to them now), component q at acc[q * kSymAcc].
 // jmi: first j of the strip minus the lane's i-particle 0 (one-sided potential).
+// last: the wave's last strip of the item.
 template <int FAM, bool LO, bool EQ, bool SYM, bool MASK, bool POT, class R, int K>
 __device__ __forceinline__ void sym_strip(const SymStage<FAM>& st, SymLane<R, K>& v, SymSums<K>& A, R e2, double* acc,
-                                          int jmi) {
+                                          int jmi, bool last) {
   const int lane = threadIdx.x & 63, l16 = lane & 15;
 #pragma unroll 1
   for (int p = 0; p < 4; ++p) {
+    if (p == 2 && last) __builtin_amdgcn_s_setprio(0);
     const int c = ((lane >> 4) + p) & 3;
     R bx = 0, by = 0, bz = 0, bp = 0;
     sym_steps<0, FAM, LO, EQ, SYM, MASK, POT, R, K>(st, 32 * c + l16, v, e2, bx, by, bz, bp, l16, -jmi - 16 * c);
@@ -446,10 +448,19 @@ __global__ __launch_bounds__(kSymBlock, 4) void k_pair_sym(Args a, SymBand band)
         wave_sync();
         sym_stage<FAM, R>(st, sym_record<FAM, R>(cur, ref, absolute, ok, lo), lo);
         wave_sync();
-        __builtin_amdgcn_s_setprio(0);
+        // Waves of equal priority are served oldest first: the younger one of a SIMD's two would end late and,
+        // alone there, run at a third of the rate.  With the priority going down in the second half of the
+        // item and again in the last half of its last strip they end together.  FP32-DS, N = 15360: 93 us
+        // -> 86; FP32 with the potential, 30011: 291 -> 266; FP32C, 12 clusters of 1024 .. 65536: 4.09 ms
+        // -> 3.85; local mode, 65536: 7.58 -> 7.24, 262144: 13.52 either way.
+        const bool last = j0 - jb + 64 * GJ >= S;
+        if (!last && 2 * (j0 - jb) < S)
+          __builtin_amdgcn_s_setprio(2);
+        else
+          __builtin_amdgcn_s_setprio(1);
         double* const sa = acc + (j0 - jc);
         const int jmi = j0 - (wb + lane);
-#define NB_STRIP(LO, EQ, SYM) sym_strip<FAM, LO, EQ, SYM, MASK, POT, R, K>(st, v, s, e2, sa, jmi)
+#define NB_STRIP(LO, EQ, SYM) sym_strip<FAM, LO, EQ, SYM, MASK, POT, R, K>(st, v, s, e2, sa, jmi, last)
         if constexpr (DS) {
           if (lo) {
             if (diag)
