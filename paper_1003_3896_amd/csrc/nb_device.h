@@ -140,14 +140,14 @@ __device__ __forceinline__ double rsqrt_f64(double x) {
   return fma(y * e, t, y);
 }
 
-// j-record of particle gi as the pair kernels consume it:
+// j-record of a particle (record64) as the pair kernels consume it:
 //   NB_FP32   (x, y, z, m) rounded to FP32 (absolute coordinates)
 //   NB_FP32C  (x - ref, m) rounded to FP32, ref = the cluster's FP64 centre of mass
 //   NB_FP32DS hi = fl32(x - ref), lo = fl32((x - ref) - hi)   (double-single coordinates)
 //   NB_FP64   (x, y, z, m) in FP64 (absolute)
-__device__ __forceinline__ void record32(const Args& a, long long gi, const double4& ref, float4& hi, float4& lo) {
-  const double x = a.pos[3 * gi], y = a.pos[3 * gi + 1], z = a.pos[3 * gi + 2];
-  const float m = (float)a.mass[gi];
+__device__ __forceinline__ void record32(const Args& a, const double4& r, const double4& ref, float4& hi, float4& lo) {
+  const double x = r.x, y = r.y, z = r.z;
+  const float m = (float)r.w;
   if (a.prec == 0) {
     hi = make_float4((float)x, (float)y, (float)z, m);
     lo = make_float4(0.0f, 0.0f, 0.0f, 0.0f);

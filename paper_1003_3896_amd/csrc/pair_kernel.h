@@ -438,6 +438,25 @@ __device__ __forceinline__ void pair32_items(const Args& a, int kick) {
     // the frame the coordinates are taken in: the cluster's centre of mass, or in the local family the
     // centre of the item's i-particle box (computed with the item's far-tile bits by the sort pass)
     // mc != 0: every mass of the cluster equals mc
+    const int ibase = item.i0 + grp * 64 * K + lane;
+    int li[K];
+    long long gidx[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      li[k] = ibase + k * 64;
+      gidx[k] = particle_index(a, c, li[k] < c.n ? li[k] : c.n - 1);
+    }
+    const int jb = item.js * c.jlen, je = min(c.n, jb + c.jlen);
+    const long long coff = LOC ? wave_uniform(c.off) : c.off;
+    // a small cluster's kernel is a chain of memory latencies: the item's first loads are issued together,
+    // before what the frame needs of the partial sums (N = 480, double-single: 9.5 us -> 8.9)
+    double4 ri[K];
+    TileRaw raw;
+    if constexpr (!LOC) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) ri[k] = record64(a, gidx[k]);
+      raw = fetch_tile<T, LOC>(a, coff, jb, min(T, je - jb));
+    }
     double4 r0;
     double mc;
     if (LOC) {
@@ -453,22 +472,13 @@ __device__ __forceinline__ void pair32_items(const Args& a, int kick) {
     const double4 ref = make_double4(wave_uniform(r0.x), wave_uniform(r0.y), wave_uniform(r0.z), 0.0);
     const int flag0 = LOC ? wave_uniform(item.flag0) : 0;
     const bool eq = mc != 0.0;
-    const int ibase = item.i0 + grp * 64 * K + lane;
     float xi[K], yi[K], zi[K], xl[K], yl[K], zl[K], qi[K];
     float ax[K], ay[K], az[K], bx[K], by[K], bz[K], pt[K], wa[K];
     double Ax[K], Ay[K], Az[K], Pt[K];
-    int li[K];
-    long long gidx[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      li[k] = ibase + k * 64;
-      gidx[k] = particle_index(a, c, li[k] < c.n ? li[k] : c.n - 1);
-    }
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const long long gi = gidx[k];
       float4 p, q;
-      record32(a, gi, ref, p, q);
+      record32(a, LOC ? record64(a, gidx[k]) : ri[k], ref, p, q);
       xi[k] = p.x;
       yi[k] = p.y;
       zi[k] = p.z;
@@ -487,9 +497,7 @@ __device__ __forceinline__ void pair32_items(const Args& a, int kick) {
       Ax[k] = Ay[k] = Az[k] = Pt[k] = 0.0;
     }
     const float e2 = c.eps2f;
-    const int jb = item.js * c.jlen, je = min(c.n, jb + c.jlen);
-    const long long coff = LOC ? wave_uniform(c.off) : c.off;
-    TileRaw raw = fetch_tile<T, LOC>(a, coff, jb, min(T, je - jb));
+    if constexpr (LOC) raw = fetch_tile<T, LOC>(a, coff, jb, min(T, je - jb));
     unsigned fw = 0;  // LOC: the far-tile bits of tiles [16 q, 16 q + 16) of this item
     for (int j0 = jb; j0 < je; j0 += T) {
       const int cnt = min(T, je - j0);
@@ -677,12 +685,6 @@ __global__ __launch_bounds__(kBlock) void k_pair64(Args a, int kick) {
   for (int it = -1; (it = next_item(a, &s_item, it)) >= 0;) {
     const PairItem item = load_item(a, it);
     const DevCluster c = load_cluster(a, item.cluster);
-    double mc;  // != 0: every mass of the cluster equals mc
-    if (small_cluster(c))
-      chunk_frame<false>(a, c, mc);
-    else
-      mc = a.mconst[item.cluster];
-    const bool eq = mc != 0.0;
     const int ibase = item.i0 + grp * 64 * K + lane;
     double xi[K], yi[K], zi[K], ax[K], ay[K], az[K], pt[K];
     int li[K];
@@ -699,6 +701,12 @@ __global__ __launch_bounds__(kBlock) void k_pair64(Args a, int kick) {
     const double e2 = c.eps2;
     const int jb = item.js * c.jlen, je = min(c.n, jb + c.jlen);
     TileRaw raw = fetch_tile<T>(a, c.off, jb, min(T, je - jb));
+    double mc;  // != 0: every mass of the cluster equals mc
+    if (small_cluster(c))
+      chunk_frame<false>(a, c, mc);
+    else
+      mc = a.mconst[item.cluster];
+    const bool eq = mc != 0.0;
     for (int j0 = jb; j0 < je; j0 += T) {
       const int cnt = min(T, je - j0);
       __syncthreads();
