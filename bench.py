@@ -3,15 +3,16 @@
 
 Default workload: a single Plummer cluster of N = 262144 equal masses (eps = 1e-4, no external
 field) advanced by the kick-drift-kick leapfrog with dt = 2^-11, pair arithmetic in mode fp32dl
-(particles sorted along a Hilbert curve, coordinates local to each work item, FP32 on far j-tiles
-and double-single on near ones, FP64-folded tile sums).  One "step" = one leapfrog step = one full
-force evaluation (N^2 pair interactions, j = i counted as the paper counts N^2) plus the O(N)
-sort, far-tile and kick/drift kernels.  Throughput is pair interactions per second of the whole step.
+(particles sorted along a Hilbert curve, coordinates local to each i-group, FP32 on far strips of
+sources and double-single on near ones, sums folded into FP64).  One "step" = one leapfrog step = one
+full force evaluation (N^2 pair interactions, j = i counted as the paper counts N^2; each unordered
+pair is computed once and serves two of them) plus the O(N) sort, combine and kick/drift kernels.  Throughput is pair interactions per second of the whole step.
 
 Prints ONE JSON line.  Besides the contract fields it carries:
-  roofline      the pair kernel (dominant, about 98% of the step) against the FP32 vector peak, with
-                its duration measured by HIP events recorded around every pair-kernel launch on
-                the stream the kernel runs on, over the timed region;
+  roofline      the pair kernels of an evaluation (about 98% of the step) against the FP32 vector peak at
+                20 flops per interaction, with their duration measured by HIP events recorded around
+                every evaluation's pair launches (the sums of rows between them included) on the
+                stream they run on, over the timed region;
   cpu_baseline  the FP64 oracle timed on this host's cores on a bounded sample of the same
                 workload (a block of rows against all N sources);
   modes         the same step timed in the other precision modes;
@@ -39,13 +40,15 @@ sys.path.insert(0, ROOT)
 FLOPS_PER_INTERACTION = 20  # the paper's convention for one pair force (Sect. 4.1)
 PEAK_FP32_TFLOPS = 157.3    # MI355X FP32 vector peak (256 CU, 2.4 GHz)
 PEAK_FP64_TFLOPS = 78.6
-# Issue-rate ceiling of the pair loop (FP32 modes, no packed FP32): a wave64 FP32 FMA every 2.9 SIMD
-# cycles and v_rsq_f32 adding 6.2 cycles at 6 waves per SIMD (timed instruction-stream
-# microbenchmark on gfx950); VALU instructions per term of the fastest loop a workload runs, counted
-# in the compiled code (the rest of the kernel, staging, folds and near tiles, only adds to it).
-CYCLES_PER_FMA, RSQ_EXTRA_CYCLES = 2.9, 6.2
-LOOP_VALU = {("fp32dl", True): 10.19, ("fp32dl", False): 12.19, ("fp32ds", True): 17.09,
-             ("fp32ds", False): 18.09}
+# Issue-rate ceiling of the symmetric pair loop (FP32 modes, clusters of 4096 .. 2^20 particles, no packed
+# FP32), which evaluates an unordered pair once for both of its particles.  SIMD cycles at the nominal
+# clock with an even number of waves per SIMD (timed instruction streams on gfx950): 2.07 per plain VALU
+# instruction, 8.1 per v_rsq_f32, 4.2 per DPP instruction (45 per 64 pairs of a lane: the row rotations);
+# VALU instructions per unordered pair of the fastest loop that a workload runs, without these two,
+# counted in the compiled code.
+CYCLES_PER_VALU, CYCLES_PER_RSQ, CYCLES_PER_DPP, DPP_PER_PAIR = 2.07, 8.1, 4.2, 45 / 64
+LOOP_VALU = {("fp32dl", True): 14.72, ("fp32dl", False): 16.72, ("fp32ds", True): 20.75,
+             ("fp32ds", False): 22.75}
 METRIC = "G pair-interactions/s & %FP32 VALU peak; batched p50/p99 job latency"
 
 
@@ -100,7 +103,7 @@ PROFILE_TAG = {"c3": "plummer262144", "c2": "salpeter65536", "c4": "ensemble512"
 
 # sources that decide what a pair-kernel launch does (its code, work items and split rule)
 PAIR_SOURCES = [os.path.join(ROOT, "paper_1003_3896_amd", "csrc", f)
-                for f in ("pair_kernel.h", "nb_device.h", "nb_internal.h", "runtime.hip")]
+                for f in ("pair_sym.h", "pair_kernel.h", "nb_device.h", "nb_internal.h", "runtime.hip")]
 
 
 def pair_source_hash():
@@ -387,13 +390,15 @@ def equal_masses(batch):
 
 def rsq_ceiling(prec, equal_masses):
     """The issue-rate ceiling of the fastest pair loop of this mode, as a fraction of the FP32 peak
-    (20 SIMD cycles per wave-interaction), or None where no loop count is recorded."""
+    (20 SIMD cycles per wave-interaction; a pair of the loop is two interactions), or None where no
+    loop count is recorded."""
     n = LOOP_VALU.get((prec, bool(equal_masses)))
     if n is None:
         return None
-    cyc = n * CYCLES_PER_FMA + RSQ_EXTRA_CYCLES
+    cyc = (n * CYCLES_PER_VALU + CYCLES_PER_RSQ + DPP_PER_PAIR * CYCLES_PER_DPP) / 2
     return {"frac": round(FLOPS_PER_INTERACTION / cyc, 4), "cycles_per_wave_interaction": round(cyc, 2),
-            "valu_per_term": n, "cycles_per_fma": CYCLES_PER_FMA, "rsq_extra_cycles": RSQ_EXTRA_CYCLES}
+            "valu_per_pair": n, "cycles_per_valu": CYCLES_PER_VALU, "cycles_per_rsq": CYCLES_PER_RSQ,
+            "dpp_per_pair": round(DPP_PER_PAIR, 3), "cycles_per_dpp": CYCLES_PER_DPP}
 
 
 def pair_roofline(prec, inter_per_eval, pair_ms, tile=None, workload="c3", equal_masses=None):
