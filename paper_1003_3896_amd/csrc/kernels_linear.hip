@@ -192,6 +192,9 @@ __global__ __launch_bounds__(kBlock) void k_update(Args a, int update) {
       }
     }
   }
+  // FP64 and pure FP32 take absolute coordinates: of the partial sums they use the mass flag alone, which
+  // the first stage of the call has left (the masses stay the same).  N = 1024, FP64: 5.4 us -> 4.2
+  if (FINISH && (a.prec == NB_FP64 || a.prec == NB_FP32)) return;
   double val[5] = {m * x[0], m * x[1], m * x[2], m, odd};
   double mn[3], mx[3];
 #pragma unroll
