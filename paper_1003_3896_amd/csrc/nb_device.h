@@ -4,14 +4,34 @@
 
 namespace nb {
 
-// Fixed-order reductions of V doubles per thread: a shuffle tree inside each wave (valid in its lane 0),
-// then over the block the waves in order (valid in thread 0).  sh needs [V] (minima and maxima: [2 V]).
+// x + (its value in the lane that the DPP control CTRL names; nothing where there is none, or in rows outside
+// ROWS).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_sum(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, ROWS, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, ROWS, 0xf, true);
+  return x + __hiloint2double(hi, lo);
+}
+
+// Fixed-order reductions of V doubles per thread: inside each wave, all of whose lanes call it (sums: valid in
+// every lane; minima and maxima: in lane 0), then over the block the waves in order (valid in thread 0).
+// sh needs [V] (minima and maxima: [2 V]).
+// Sums go by DPP row shifts and row broadcasts: the kernels of small clusters are chains of latencies, and a
+// shuffle through the LDS takes several times as long as the addition (N = 480, 8 steps: 134.0 -> 130.9 us).
 template <int V>
 __device__ __forceinline__ void wave_sum(double (&val)[V]) {
 #pragma unroll
-  for (int m = 32; m >= 1; m >>= 1)
-#pragma unroll
-    for (int q = 0; q < V; ++q) val[q] += __shfl_down(val[q], m);
+  for (int q = 0; q < V; ++q) {
+    double x = val[q];
+    x = dpp_sum<0x111, 0xf>(x);  // row_shr:1, 2, 4, 8: lane 15 of a row holds its sum
+    x = dpp_sum<0x112, 0xf>(x);
+    x = dpp_sum<0x114, 0xf>(x);
+    x = dpp_sum<0x118, 0xf>(x);
+    x = dpp_sum<0x142, 0xa>(x);  // row_bcast:15 into rows 1 and 3
+    x = dpp_sum<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3: lane 63 holds the wave's
+    val[q] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 63),
+                              __builtin_amdgcn_readlane(__double2loint(x), 63));
+  }
 }
 template <int V>
 __device__ __forceinline__ void wave_minmax(double (&mn)[V], double (&mx)[V]) {
@@ -180,7 +200,7 @@ __device__ __forceinline__ double chunk_sum(const Args& a, const DevCluster& c, 
 // Reference point (centre of mass) and common mass of a small cluster, by each wave that needs them: without
 // the launch of k_reduce, which cost more (3.3 us per evaluation) than the microsecond that this takes at the
 // start of an item.  (The symmetric kernel has more items and chunks: there it cost N = 15360 7 us to
-// save 5, and the 512-cluster ensemble 5%.)  Called by whole waves; the point is valid in lane 0.
+// save 5, and the 512-cluster ensemble 5%.)  Called by whole waves.
 template <bool CENTRE>
 __device__ __forceinline__ double4 chunk_frame(const Args& a, const DevCluster& c, double& mc) {
   const int lane = threadIdx.x & 63;
@@ -191,10 +211,7 @@ __device__ __forceinline__ double4 chunk_frame(const Args& a, const DevCluster& 
   double v[4];
 #pragma unroll
   for (int d = 0; d < 4; ++d) v[d] = has ? p[d] : 0.0;
-#pragma unroll
-  for (int s = kSymMin / kChunk / 2; s >= 1; s >>= 1)
-#pragma unroll
-    for (int d = 0; d < 4; ++d) v[d] += __shfl_down(v[d], s);
+  wave_sum<4>(v);
   return v[3] > 0.0 ? make_double4(v[0] / v[3], v[1] / v[3], v[2] / v[3], v[3]) : make_double4(0.0, 0.0, 0.0, 0.0);
 }
 
