@@ -343,12 +343,14 @@ __device__ __forceinline__ void combine_split(const Args& a, const Chunk& ch, co
   if (potmode && a.pot) a.pot[gi] = r32 ? (double)(-(float)a.G * (float)pt) : -a.G * pt;
 }
 
-// One band of the symmetric path; after a cluster's last band the particle is finished.  Block (x, y) as in
-// k_update.
+// Symmetric cluster: the rows of `band` into the running sums, which the clusters that end with that band (or
+// had fewer) leave to the pass that finishes them; or, with band < 0, the cluster's own last band and the end of
+// its stage.  Exactly one pass finishes a cluster: this one, or k_update between two stages.  Block (x, y)
+// as in k_update.
 template <int NC>
 __device__ __forceinline__ void combine_sym(const Args& a, const Chunk& ch, const DevCluster& c, int band, int kick,
                                             double (*sh)[4][64]) {
-  if (band < 0 || band >= sym_rows(c.n, c.nseg, NC == 4, c.sym_doubles).nbands) return;
+  if (band >= 0 && band >= sym_rows(c.n, c.nseg, NC == 4, c.sym_doubles).nbands - 1) return;
   const int Q = sym_sums(c.n), t = threadIdx.x;
   if (Q == 1 && blockIdx.y) return;
   const int q = Q == 1 ? 0 : t >> 6, e = Q == 1 ? t : 64 * blockIdx.y + (t & 63);
@@ -370,22 +372,23 @@ __device__ __forceinline__ void combine_sym(const Args& a, const Chunk& ch, cons
 }
 
 template <int NC>
-__global__ __launch_bounds__(kBlock) void k_combine(Args a, int band, int kick, CombineOneSided which) {
+__global__ __launch_bounds__(kBlock) void k_combine(Args a, CombineWhat what, int band, int kick) {
   __shared__ double sh[NC][4][64];
   const Chunk ch = load_chunk(a);
   const DevCluster c = load_cluster(a, ch.cluster);
-  if (c.seg)
-    combine_sym<NC>(a, ch, c, band, kick, sh);
-  else if (blockIdx.y == 0 && (which == kCombineAll || (which == kCombineLarge && !small_cluster(c))))
+  if (c.seg) {
+    if (what != kCombineLarge) combine_sym<NC>(a, ch, c, what == kCombineBand ? band : -1, kick, sh);
+  } else if (blockIdx.y == 0 && (what == kCombineAll || (what == kCombineLarge && !small_cluster(c)))) {
     combine_split(a, ch, c, NC == 4, kick);
+  }
 }
 
-hipError_t launch_combine(const Args& a, int band, bool potmode, bool kick, CombineOneSided which, hipStream_t s) {
+hipError_t launch_combine(const Args& a, CombineWhat what, int band, bool potmode, bool kick, hipStream_t s) {
   const dim3 grid(a.nchunks, a.sym ? 4 : 1);
   if (potmode)
-    hipLaunchKernelGGL(k_combine<4>, grid, dim3(kBlock), 0, s, a, band, kick ? 1 : 0, which);
+    hipLaunchKernelGGL(k_combine<4>, grid, dim3(kBlock), 0, s, a, what, band, kick ? 1 : 0);
   else
-    hipLaunchKernelGGL(k_combine<3>, grid, dim3(kBlock), 0, s, a, band, kick ? 1 : 0, which);
+    hipLaunchKernelGGL(k_combine<3>, grid, dim3(kBlock), 0, s, a, what, band, kick ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -228,9 +228,11 @@ hipError_t launch_reduce(const Args& a, int B, hipStream_t s);
 hipError_t launch_pair(const Args& a, const TileCfg& t, int grid, bool mask, bool potmode, bool kick,
                        hipStream_t s);
 hipError_t launch_energy(const Args& a, hipStream_t s);
-// one band of the symmetric path (-1: none), and the sums of the one-sided clusters named
-enum CombineOneSided { kCombineNone, kCombineLarge, kCombineAll };
-hipError_t launch_combine(const Args& a, int band, bool potmode, bool kick, CombineOneSided which, hipStream_t s);
+// kCombineBand: the running sums of the symmetric clusters that have bands after `band`.  kCombineAll ends the
+// stage of every cluster that the pair kernels have not finished (symmetric: from its own last band);
+// kCombineLarge only of the one-sided ones above the symmetric path.
+enum CombineWhat { kCombineBand, kCombineLarge, kCombineAll };
+hipError_t launch_combine(const Args& a, CombineWhat what, int band, bool potmode, bool kick, hipStream_t s);
 hipError_t launch_pair_sym(const Args& a, const SymBand& b, int grid, bool mask, bool potmode, hipStream_t s);
 hipError_t launch_sym_f32(const Args& a, const SymBand& b, int grid, bool mask, bool pot, hipStream_t s);
 hipError_t launch_sym_ds(const Args& a, const SymBand& b, int grid, bool mask, bool pot, hipStream_t s);

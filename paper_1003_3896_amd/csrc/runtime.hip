@@ -660,8 +660,7 @@ int pair_launch(nbody_ctx* ctx, const Prepared& P, const OneSided& o, int counte
 // The last (or only) combine pass of an evaluation; all = false: for the clusters that the fused pass
 // between two stages leaves out.
 int combine(const Prepared& P, bool potmode, bool kick, bool all, hipStream_t s) {
-  const hipError_t e = launch_combine(P.a, all && !P.bands.empty() ? P.bands.back().index : -1, potmode, kick,
-                                      all ? kCombineAll : kCombineLarge, s);
+  const hipError_t e = launch_combine(P.a, all ? kCombineAll : kCombineLarge, 0, potmode, kick, s);
   if (e != hipSuccess) return fail(NB_ERR_HIP, "combine kernel launch: %s", hipGetErrorString(e));
   return NB_OK;
 }
@@ -671,6 +670,7 @@ int combine(const Prepared& P, bool potmode, bool kick, bool all, hipStream_t s)
 // with a combine pass after every band but the last.  Per-kernel timing spans the pair kernels.
 // `again`: masses and system are those of the evaluation before in the same call, so the modes that need
 // neither reference points nor boxes keep its common masses and skip the reduction (4 us).
+// The pass that follows (combine or the fused update) adds each cluster's last band and ends its stage.
 int pair_pass(nbody_ctx* ctx, Prepared& P, bool potmode, bool kick, bool again, hipStream_t s) {
   hipError_t e;
   const Plan& p = ctx->plan;
@@ -696,7 +696,7 @@ int pair_pass(nbody_ctx* ctx, Prepared& P, bool potmode, bool kick, bool again, 
     e = launch_pair_sym(P.a, band, std::min(band.nitems, ctx->cus * kSymBlocksPerCu), p.anymask, potmode, s);
     if (e != hipSuccess) return fail(NB_ERR_HIP, "pair kernel launch: %s", hipGetErrorString(e));
     if (b == nbands - 1 || P.bands[b + 1].index == band.index) continue;
-    e = launch_combine(P.a, band.index, potmode, kick, kCombineNone, s);
+    e = launch_combine(P.a, kCombineBand, band.index, potmode, false, s);
     if (e != hipSuccess) return fail(NB_ERR_HIP, "combine kernel launch: %s", hipGetErrorString(e));
   }
   if (ctx->timing) {
