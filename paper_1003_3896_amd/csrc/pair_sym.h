@@ -181,22 +181,27 @@ __device__ __forceinline__ void sym_steps(const SymStage<FAM>& st, int e0, SymLa
       r2 = fma_sym(dy, dy, r2);
       r2 = fma_sym(dz, dz, r2);
       const R inv = rsq_sym(r2);
-      R s = inv * (inv * inv);
-      if (MASK) s = r2 > R(0) ? s : R(0);
-      const R si = EQ ? s : s * j.m;  // equal masses: the mass is applied once, in the combine pass
+      // si, sj: r^-3 times the other particle's mass; qi, qj: r^-1 times it (potential).  Equal masses: the mass is
+      // applied once, in the combine pass.  The FP32 families take the mass into the first factor: r^-3 alone
+      // leaves their range for |d| outside 1e-12 .. 1e12 (one product more per pair: 65536 Salpeter stars, a
+      // leapfrog step, 1.01 -> 1.05 ms in NB_FP32DL and 1.12 -> 1.16 in NB_FP32DS).
+      constexpr bool RANGE = !EQ && sizeof(R) == 4;
+      const R inv2 = inv * inv, s = inv * inv2;
+      const R qi = EQ ? inv : j.m * inv, qj = EQ ? inv : v.m[k] * inv;
+      R si = RANGE ? qi * inv2 : EQ ? s : s * j.m, sj = RANGE ? qj * inv2 : EQ ? s : s * v.m[k];
+      if (MASK) {
+        si = r2 > R(0) ? si : R(0);
+        sj = r2 > R(0) ? sj : R(0);
+      }
       v.ax[k] = fma_sym(dx, si, v.ax[k]);
       v.ay[k] = fma_sym(dy, si, v.ay[k]);
       v.az[k] = fma_sym(dz, si, v.az[k]);
-      if constexpr (POT) {
-        const R q = EQ ? inv : inv * j.m;
-        v.p[k] += (SYM || ((l16 + N) & 15) != self0 + 64 * k) ? q : R(0);
-      }
+      if constexpr (POT) v.p[k] += (SYM || ((l16 + N) & 15) != self0 + 64 * k) ? qi : R(0);
       if constexpr (SYM) {
-        const R sj = EQ ? s : s * v.m[k];
         tx = k ? fma_sym(dx, sj, tx) : dx * sj;
         ty = k ? fma_sym(dy, sj, ty) : dy * sj;
         tz = k ? fma_sym(dz, sj, tz) : dz * sj;
-        if constexpr (POT) tp = EQ ? (k ? tp + inv : inv) : (k ? fma_sym(inv, v.m[k], tp) : inv * v.m[k]);
+        if constexpr (POT) tp = !k ? qj : EQ ? tp + qj : fma_sym(inv, v.m[k], tp);
       }
     }
     if constexpr (SYM) {
