@@ -216,7 +216,7 @@ __device__ __forceinline__ void lds_add(double* p, double x) {
   __hip_atomic_fetch_add(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);  // ds_add_f64
 }
 
-// FP64 sums of one lane's i-particles (the FP32 sums are folded into them every 32 terms, the FP64
+// FP64 sums of one lane's i-particles (the FP32 sums are folded into them every 16 or 32 terms, the FP64
 // family adds to them directly).
 template <int K>
 struct SymSums {
@@ -259,8 +259,13 @@ __device__ __forceinline__ void sym_strip(const SymStage<FAM>& st, SymLane<R, K>
       lds_add(a + 2 * kSymAcc<POT>, (double)bz);
       if constexpr (POT) lds_add(a + 3 * kSymAcc<POT>, (double)bp);
     }
+    // Into FP64 every 32 terms; every 16 in near strips of the local mode, whose sorted order puts a particle's
+    // near neighbours one after the other: a sum then grows early and rounds all that follow at its size (the
+    // one-sided kernel deals successive terms to two sums).  Mean error of FP32DL accelerations, uniform
+    // sphere of 9000: 4.81e-8 with 32, 4.06e-8 with 16, one-sided kernel 4.60e-8; far strips with 16 too:
+    // 4.05e-8, but N = 65536 takes 988 us for 958 (954 with 32).
     if constexpr (FAM != FAM_F64) {
-      if (p & 1) sym_fold<POT, K>(v, A);
+      if ((FAM == FAM_DL && LO) || (p & 1)) sym_fold<POT, K>(v, A);
     }
   }
 }
