@@ -199,8 +199,9 @@ __device__ __forceinline__ double chunk_sum(const Args& a, const DevCluster& c, 
 
 // Reference point (centre of mass) and common mass of a small cluster, by each wave that needs them: without
 // the launch of k_reduce, which cost more (3.3 us per evaluation) than the microsecond that this takes at the
-// start of an item.  (The symmetric kernel has more items and chunks: there it cost N = 15360 7 us to
-// save 5, and the 512-cluster ensemble 5%.)  Called by whole waves.
+// start of an item, unless the items are many (kReduceItems) or other clusters need k_reduce anyway: then the
+// kernels read its results, which are the same bits.  (The symmetric kernel has more items and chunks: there it
+// cost N = 15360 7 us to save 5, and the 512-cluster ensemble 5%.)  Called by whole waves.
 template <bool CENTRE>
 __device__ __forceinline__ double4 chunk_frame(const Args& a, const DevCluster& c, double& mc) {
   const int lane = threadIdx.x & 63;

@@ -186,6 +186,7 @@ struct Args {
   int jtile;           // j-records of one LDS tile (T)
   double* mconst;      // [B] the common mass of a cluster whose masses are all equal, else 0
   double4* ref;        // [B] reference point of each cluster (centre of mass), w = total mass
+  int reduced;         // ref and mconst hold the small clusters too (else: chunk_frame)
   double4* part;       // partial sums (ax, ay, az, pot) of split clusters
   double* sym;         // partial-sum rows of the symmetric path's clusters
   double4* gbox;       // [nchunks] centre of each sorted chunk's box, w = (3/4 diagonal)^2 (NB_FP32DL)

@@ -462,7 +462,7 @@ __device__ __forceinline__ void pair32_items(const Args& a, int kick) {
     if (LOC) {
       r0 = a.ibox[it];
       mc = a.mconst[item.cluster];
-    } else if (small_cluster(c)) {
+    } else if (small_cluster(c) && !a.reduced) {
       r0 = chunk_frame<FAM != FAM_F32 || FOLD>(a, c, mc);
       mc = wave_uniform(mc);
     } else {
@@ -702,7 +702,7 @@ __global__ __launch_bounds__(kBlock) void k_pair64(Args a, int kick) {
     const int jb = item.js * c.jlen, je = min(c.n, jb + c.jlen);
     TileRaw raw = fetch_tile<T>(a, c.off, jb, min(T, je - jb));
     double mc;  // != 0: every mass of the cluster equals mc
-    if (small_cluster(c))
+    if (small_cluster(c) && !a.reduced)
       chunk_frame<false>(a, c, mc);
     else
       mc = a.mconst[item.cluster];

@@ -91,6 +91,7 @@ struct Plan {
   bool anymask = false;
   bool anysplit = false;  // some one-sided cluster is finished by the combine pass (split, or kFlagDefer)
   bool reduce = false;    // some cluster needs k_reduce (is not small)
+  int nsmall = 0;         // small clusters
   int maxn_small = 0, maxn_large = 0;  // largest one-sided cluster below and above the symmetric path
   std::vector<int> sym;   // clusters on the symmetric path, largest first
   int ndelta = 0;         // segment distances of the largest of them (bounds its bands)
@@ -323,6 +324,7 @@ int build_plan(const nbody_system* sys, Plan& p, size_t limit = 0) {
   const bool sorted = sys->prec == NB_FP32DL;
   p.anymask = false;
   p.anysplit = p.reduce = false;
+  p.nsmall = 0;
   p.maxn_small = p.maxn_large = 0;
   Counts m, one;  // one: every cluster on the one-sided path
   long long want = 0, least = 0;
@@ -376,6 +378,7 @@ int build_plan(const nbody_system* sys, Plan& p, size_t limit = 0) {
       (small_cluster(c) ? p.maxn_small : p.maxn_large) = std::max(small_cluster(c) ? p.maxn_small : p.maxn_large, c.n);
     }
     p.reduce |= !small_cluster(c);
+    p.nsmall += small_cluster(c);
     c.rec0 = (int)m.nrecords;
     m.nrecords += (long long)c.nchunks * chunk_records(c.n, c.seg);
     if (sorted) m.nstiles += (c.n + kSortTile - 1) / kSortTile;
@@ -534,6 +537,13 @@ Slot* fixed_slot(nbody_ctx* ctx, size_t bytes, int* rc) {
   return &s;
 }
 
+// Items of small clusters per CU, beyond one per cluster, above which k_reduce forms their frames.  It costs a launch
+// (3 to 6 us) and works once per cluster; chunk_frame costs every item a microsecond of latency.  FP32C, a
+// leapfrog step without -> with it: 8 clusters of 256..2047 particles (240 items) 16.8 -> 18.9 us, 4000 of
+// 20..300 (4400) 127 -> 134, 64 of 256..2047 (1300) 52.8 -> 53.1, 256 (5200) 138 -> 133, 1000 456 -> 429, 64 of
+// 2048..4095 (6000) 235 -> 229.
+constexpr int kReduceItems = 16;
+
 int prepare(nbody_ctx* ctx, const nbody_system* sys, void* ws, size_t ws_bytes, const double* coef3,
             Prepared& P, hipStream_t stream, bool pot = false, int rounds = 1, bool fixed = false) {
   Plan& p = ctx->plan;
@@ -611,6 +621,7 @@ int prepare(nbody_ctx* ctx, const nbody_system* sys, void* ws, size_t ws_bytes, 
   a.jtile = lg.tile.tile;
   a.mconst = reinterpret_cast<double*>(w + L.mconst);
   a.ref = reinterpret_cast<double4*>(w + L.ref);
+  a.reduced = p.reduce || sm.nitems - p.nsmall > kReduceItems * ctx->cus;
   a.epart = reinterpret_cast<double*>(w + L.epart);
   a.pot_ws = reinterpret_cast<double*>(w + L.pot);
   a.eacc_ws = reinterpret_cast<double*>(w + L.eacc);
@@ -675,7 +686,7 @@ int pair_pass(nbody_ctx* ctx, Prepared& P, bool potmode, bool kick, bool again, 
   hipError_t e;
   const Plan& p = ctx->plan;
   int rc;
-  if (p.reduce && (P.centred || !again) && (e = launch_reduce(P.a, p.B, s)) != hipSuccess)
+  if (P.a.reduced && (P.centred || !again) && (e = launch_reduce(P.a, p.B, s)) != hipSuccess)
     return fail(NB_ERR_HIP, "reduce kernel launch: %s", hipGetErrorString(e));
   if (P.a.nstiles) {
     e = launch_sort(P.a, p.B, s);  // also the work items' boxes and far-tile bits
