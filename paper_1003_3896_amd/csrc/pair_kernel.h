@@ -44,17 +44,21 @@ template <int FAM, int T>
 struct PairLds;
 template <int T>
 struct PairLds<FAM_F32, T> {
+  static constexpr bool kLocal = false;
   float4 hi[T];
   __device__ const float4& lo_at(int i) const { return hi[i]; }  // unused by the FP32 family
 };
 template <int T>
 struct PairLds<FAM_DS, T> {
+  static constexpr bool kLocal = false;
   float4 hi[T];
   float4 lo[T];
   __device__ const float4& lo_at(int i) const { return lo[i]; }
 };
 template <int T>
-struct PairLds<FAM_DL, T> : PairLds<FAM_DS, T> {};
+struct PairLds<FAM_DL, T> : PairLds<FAM_DS, T> {
+  static constexpr bool kLocal = true;
+};
 template <int T>
 struct PairLds<FAM_F64, T> {
   double4 r[T];
@@ -275,11 +279,25 @@ __device__ __forceinline__ void reduce_and_finish(const Args& a, const DevCluste
 // ---------------------------------------------------------------------------------------------
 // FP32 and double-single families
 
+// v_rsq_f32 and the wait state that its consumer needs, always as an s_nop next to it.  The two waves that a SIMD
+// issues plain instructions of in turn fall back into step there; when the compiler fills the wait state with
+// another instruction, all of the loop issues slower (pair_sym.h).  Leapfrog step, 256 clusters of 2048..4095
+// particles: FP32C 799 -> 748 us, FP32DS 1009 -> 976; evaluations with the potential 983 -> 872 and 1188 -> 1102;
+// an s_nop before it too: 748 and 976, but 64 such clusters in FP32 205 -> 212.  The local family (LOCAL), with six
+// waves per SIMD, is the faster without (N = 1100000: 308 ms, 310 with).
+template <bool LOCAL>
+__device__ __forceinline__ float rsq32(float x) {
+  if constexpr (LOCAL) return __builtin_amdgcn_rsqf(x);
+  float r;
+  asm("v_rsq_f32_e32 %0, %1\n\ts_nop 0" : "=v"(r) : "v"(x));
+  return r;
+}
+
 // One j-record against the K i-particles of this lane:
 //   d = x_j - x_i (double-single: (hi_j - hi_i) + (lo_j - lo_i)),  r2 = |d|^2 + eps^2,
 //   s = m_j r2^{-3/2},  a += s d,  and with POT  pot += m_j r2^{-1/2} for j != i
 // (EQ: all masses of the cluster are equal, m_j is left out here and multiplied in once later).
-template <bool DS, int K, bool MASK, bool POT, bool EQ>
+template <bool DS, int K, bool MASK, bool POT, bool EQ, bool LOCAL>
 __device__ __forceinline__ void interact32(const float4 pj, const float4 pl, const float (&xi)[K], const float (&yi)[K],
                                            const float (&zi)[K], const float (&xl)[K], const float (&yl)[K],
                                            const float (&zl)[K], float e2, float (&ax)[K], float (&ay)[K],
@@ -295,7 +313,7 @@ __device__ __forceinline__ void interact32(const float4 pj, const float4 pl, con
     float r2 = fmaf(dx, dx, e2);
     r2 = fmaf(dy, dy, r2);
     r2 = fmaf(dz, dz, r2);
-    const float inv = __builtin_amdgcn_rsqf(r2);
+    const float inv = rsq32<LOCAL>(r2);
     const float mi = EQ ? inv : pj.w * inv;  // equal masses: m_j is applied once, after the sum
     float s = mi * (inv * inv);
     if (MASK) s = r2 > 0.0f ? s : 0.0f;
@@ -365,7 +383,7 @@ __device__ __forceinline__ void full_tile_terms(const LDS& sh, int u0, int j0, c
     for (int u = u0; u < u0 + TW; u += 8) {
 #pragma unroll
       for (int v = 0; v < 8; ++v)
-        interact32<DS, K, MASK, POT, EQ>(sh.hi[u + v], sh.lo_at(u + v), xi, yi, zi, xl, yl, zl, e2,
+        interact32<DS, K, MASK, POT, EQ, LDS::kLocal>(sh.hi[u + v], sh.lo_at(u + v), xi, yi, zi, xl, yl, zl, e2,
                                          (v & 1) ? bx : ax, (v & 1) ? by : ay, (v & 1) ? bz : az, pt, li,
                                          j0 + u + v);
     }
@@ -571,7 +589,7 @@ __device__ __forceinline__ void pair32_items(const Args& a, int kick) {
         for (int u = u0; u < u0 + mine; u += 8) {
 #pragma unroll
           for (int v = 0; v < 8; ++v)
-            interact32<DS, K, MASK, POT, false>(sh.hi[u + v], sh.lo_at(u + v), xi, yi, zi, xl, yl, zl, e2,
+            interact32<DS, K, MASK, POT, false, LOC>(sh.hi[u + v], sh.lo_at(u + v), xi, yi, zi, xl, yl, zl, e2,
                                                 (v & 1) ? bx : ax, (v & 1) ? by : ay, (v & 1) ? bz : az, pt, li,
                                                 j0 + u + v);
         }
