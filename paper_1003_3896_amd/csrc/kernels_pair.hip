@@ -13,18 +13,14 @@ bool tile_supported(int family, const TileCfg& t) {
   return kw && ph && (t.tile == 128 || t.tile == 256) && t.bpc >= 1 && t.bpc <= 8;
 }
 
-hipError_t launch_pair(const Args& a, const TileCfg& t, int grid, bool mask, bool potmode, bool kick,
-                       hipStream_t s) {
-  PairFn fn = nullptr;
-  if (a.prec == 4)
-    fn = pair_kernel_dl(t, true, mask, potmode);
-  else if (a.prec == 3)
-    fn = pair_kernel_f64(t, true, mask, potmode);
-  else if (a.prec == 2)
-    fn = pair_kernel_ds(t, true, mask, potmode);
-  else
-    fn = pair_kernel_f32(t, a.prec != 0, mask, potmode);  // pure FP32 (0) keeps one FP32 sum
-  if (!fn) return hipErrorInvalidValue;
+PairFn pair_kernel(int prec, const TileCfg& t, bool mask, bool potmode) {
+  if (prec == 4) return pair_kernel_dl(t, true, mask, potmode);
+  if (prec == 3) return pair_kernel_f64(t, true, mask, potmode);
+  if (prec == 2) return pair_kernel_ds(t, true, mask, potmode);
+  return pair_kernel_f32(t, prec != 0, mask, potmode);  // pure FP32 (0) keeps one FP32 sum
+}
+
+hipError_t launch_pair(PairFn fn, const Args& a, int grid, bool kick, hipStream_t s) {
   hipLaunchKernelGGL(fn, dim3(grid), dim3(kBlock), 0, s, a, kick ? 1 : 0);
   return hipGetLastError();
 }

@@ -226,8 +226,10 @@ hipError_t launch_update(const Args& a, bool update, bool finish, hipStream_t s)
 // reference point, common mass and box of every cluster from the chunk partials
 hipError_t launch_reduce(const Args& a, int B, hipStream_t s);
 
-hipError_t launch_pair(const Args& a, const TileCfg& t, int grid, bool mask, bool potmode, bool kick,
-                       hipStream_t s);
+// the one-sided pair kernel of a mode and shape (null: not compiled in)
+typedef void (*PairFn)(Args, int);
+PairFn pair_kernel(int prec, const TileCfg& t, bool mask, bool potmode);
+hipError_t launch_pair(PairFn fn, const Args& a, int grid, bool kick, hipStream_t s);
 hipError_t launch_energy(const Args& a, hipStream_t s);
 // kCombineBand: the running sums of the symmetric clusters that have bands after `band`.  kCombineAll ends the
 // stage of every cluster that the pair kernels have not finished (symmetric: from its own last band);
@@ -247,7 +249,6 @@ bool tile_supported(int family, const TileCfg& t);
 // i-particles of one pair work item for a shape
 inline int item_tile(const TileCfg& t) { return 64 * t.k * (4 / t.w); }
 
-typedef void (*PairFn)(Args, int);
 PairFn pair_kernel_f32(const TileCfg& t, bool fold, bool mask, bool pot);
 PairFn pair_kernel_ds(const TileCfg& t, bool fold, bool mask, bool pot);
 PairFn pair_kernel_f64(const TileCfg& t, bool fold, bool mask, bool pot);

@@ -170,6 +170,7 @@ struct nbody_ctx {
   hipStream_t gstream = nullptr;  // non-blocking stream the step graphs are captured on
   std::vector<StepGraph> gcache;  // small LRU cache of captured graphs (most recent last)
   TileCfg tiles[kFamilies][kSizeClasses];
+  std::vector<std::pair<PairFn, int>> resident;  // resident_blocks
   Slot slots[4];
   int next_slot = 0;
   bool timing = false;
@@ -650,6 +651,18 @@ hipEvent_t pool_event(nbody_ctx* ctx) {
   return e;
 }
 
+// Blocks of a one-sided pair kernel that a CU holds at once.
+int resident_blocks(nbody_ctx* ctx, PairFn fn) {
+  for (const auto& r : ctx->resident)
+    if (r.first == fn) return r.second;
+  int n = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void*>(fn), kBlock, 0) != hipSuccess ||
+      n < 1)
+    n = 1;
+  ctx->resident.emplace_back(fn, n);
+  return n;
+}
+
 int pair_launch(nbody_ctx* ctx, const Prepared& P, const OneSided& o, int counter, bool potmode, bool kick,
                 hipStream_t s) {
   if (!o.nitems) return NB_OK;
@@ -662,8 +675,10 @@ int pair_launch(nbody_ctx* ctx, const Prepared& P, const OneSided& o, int counte
     a.prec = o.prec;
     a.spos = nullptr;
   }
-  const int grid = std::max(1, std::min(o.nitems, ctx->cus * o.tile.bpc));
-  const hipError_t e = launch_pair(a, o.tile, grid, ctx->plan.anymask, potmode, kick, s);
+  const PairFn fn = pair_kernel(a.prec, o.tile, ctx->plan.anymask, potmode);
+  if (!fn) return fail(NB_ERR_HIP, "pair kernel launch: shape not compiled in");
+  const int bpc = std::min(o.tile.bpc, resident_blocks(ctx, fn));
+  const hipError_t e = launch_pair(fn, a, std::min(o.nitems, ctx->cus * bpc), kick, s);
   if (e != hipSuccess) return fail(NB_ERR_HIP, "pair kernel launch: %s", hipGetErrorString(e));
   return NB_OK;
 }
