@@ -1,4 +1,5 @@
-"""Tile-shape autotuner for the pair kernel.
+"""Tile-shape autotuner for the one-sided pair kernel (clusters of fewer than 4096 or more than 2^20
+particles; the symmetric kernel between them has one fixed shape).
 
 For one workload (a ragged batch) and precision mode, time every compiled-in launch shape
 (k i-particles per lane, waves per i-group, LDS tile, blocks per CU) with the library's own
@@ -43,14 +44,28 @@ def size_class(maxn: int) -> int:
     return 0 if maxn < 2048 else 1 if maxn < 32768 else 2 if maxn < 131072 else 3
 
 
+# cluster sizes of the symmetric path (kSymMin, kSymMax in csrc/nb_internal.h)
+SYM_MIN, SYM_MAX = 4096, 1 << 20
+
+
+def one_sided(offsets) -> np.ndarray:
+    """Sizes of the clusters whose launch the shapes decide."""
+    n = np.diff(np.asarray(offsets))
+    return n[(n < SYM_MIN) | (n > SYM_MAX)]
+
+
 def sweep(batch, prec: str, shapes=None, tiles=None, bpcs=None, reps: int = 3, sample: int = 4096,
           device: int = 0) -> List[Dict]:
-    """Time and check every shape for one workload; returns one dict per shape."""
+    """Time and check every shape for one workload, all of whose clusters must take the one-sided kernel (the
+    time of any other would not depend on the shape); returns one dict per shape."""
+    sizes = one_sided(batch.offsets)
+    if len(sizes) != batch.B:
+        raise ValueError("launch shapes decide nothing for clusters of %d to %d particles" % (SYM_MIN, SYM_MAX))
     import torch
     shapes = shapes or SHAPES
     tiles = tiles or TILES
     bpcs = bpcs or BLOCKS_PER_CU
-    nclass = size_class(int(np.diff(batch.offsets).max()))
+    nclass = size_class(int(sizes.max()))
     ref = nbody.Simulation(batch, "fp64", device)
     ref.accel()
     rng = np.random.default_rng(0)
@@ -145,19 +160,20 @@ def apply(ctx, arch: str = "gfx950", path: str = CACHE, fixed_tile: Optional[Dic
 
 
 def representative(nclass: int):
-    """A workload of each size class: small ragged ensemble, the C4-like ensemble, the C2 cluster
-    (65536 Salpeter stars), the C3 cluster (262144)."""
+    """A workload of each size class: ragged ensembles of 256 clusters on either side of 2048 particles, and
+    one cluster above the symmetric path.  No one-sided cluster falls in class 2 (65536 Salpeter stars), which
+    is not tuned."""
     from . import inputs
     if nclass == 0:
         return inputs.c4(B=256, lo=256, hi=2047)
     if nclass == 1:
-        return inputs.c4()
+        return inputs.c4(B=256, lo=2048, hi=SYM_MIN - 1)
     if nclass == 2:
         return inputs.c2()
-    return inputs.c3()
+    return inputs.c3(1100000)
 
 
-def tune_all(precs=("fp32c", "fp32ds", "fp64", "fp32dl"), classes=(0, 1, 2, 3), path: str = CACHE, verbose: bool = True) -> Dict:
+def tune_all(precs=("fp32c", "fp32ds", "fp64", "fp32dl"), classes=(0, 1, 3), path: str = CACHE, verbose: bool = True) -> Dict:
     """Sweep every (precision family, size class) on its representative workload and cache the
     fastest shape that passes the accuracy gate."""
     out = {}
