@@ -556,10 +556,13 @@ int prepare(nbody_ctx* ctx, const nbody_system* sys, void* ws, size_t ws_bytes, 
   lg.nitems = sm.first = (int)items.size();
   sm.prec = sys->prec == NB_FP32DL ? NB_FP32DS : sys->prec;
   sm.tile = ctx->tiles[family_of(sys->prec)][size_class(p.maxn_small)];
+  // one i-particle per lane in place of two (it does not change a result): in FP64 with the potential where
+  // two waves share a group (256 clusters of 2048..4095: 1795 -> 1756 us; with four, 1809 -> 1868, and without
+  // the potential two are faster, 1501 to 1550), and where there are fewer than two items per CU, halves of
+  // which fill the chip better
+  if (sm.prec == NB_FP64 && pot && sm.tile.k == 2 && sm.tile.w == 2) sm.tile.k = 1;
   if (p.maxn_small) {
     make_items(p, sm.tile, items, true, false);
-    // fewer than two items per CU: halves of them fill the chip better (the i-particles per lane do not
-    // change a result)
     if ((int)items.size() - sm.first < 2 * ctx->cus && sm.tile.k == 2) {
       sm.tile.k = 1;
       sm.tile.phase = 0;
