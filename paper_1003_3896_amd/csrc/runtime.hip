@@ -68,8 +68,14 @@ const Sym6 kSym6;
 // process ends.  Host code must never pass `scratch` itself to a kernel or copy (on the host the
 // name is a stand-in, not a device address): the address of each device's copy is looked up once
 // per device with hipGetSymbolAddress and kept in g_scratch.
-constexpr size_t kScratchBytes = NB_NOALLOC_SCRATCH_BYTES;
-constexpr size_t kScratchTableBytes = NB_NOALLOC_TABLE_BYTES;  // pinned staging of its tables
+// The limits NB_NOALLOC_SCRATCH_BYTES and NB_NOALLOC_TABLE_BYTES are stated for the layout in which every cluster
+// is split into j-ranges and described by kLimitCluster bytes.  What is uploaded and used beyond that is the
+// rest of its descriptor, at most 621 KB for the 38,836 clusters that the table limit lets through, and a
+// counter per band: it has the room of kBeyondLimit.
+constexpr size_t kLimitCluster = 72, kBeyondLimit = 1 << 20;
+constexpr size_t kScratchBytes = NB_NOALLOC_SCRATCH_BYTES + kBeyondLimit;
+constexpr size_t kScratchTableBytes = NB_NOALLOC_TABLE_BYTES + kBeyondLimit;  // pinned staging of its tables
+static_assert(sizeof(DevCluster) <= kLimitCluster + 16, "kBeyondLimit");
 constexpr int kMaxDevices = 64;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 std::mutex g_scratch_mu;
@@ -95,7 +101,7 @@ struct Plan {
   int maxn_small = 0, maxn_large = 0;  // largest one-sided cluster below and above the symmetric path
   std::vector<int> sym;   // clusters on the symmetric path, largest first
   int ndelta = 0;         // segment distances of the largest of them (bounds its bands)
-  size_t onesided = 0;    // workspace bytes if every cluster took the one-sided path
+  size_t onesided = 0;    // workspace bytes if every cluster took the one-sided path (kLimitCluster)
   size_t onesided_blob = 0;
   std::vector<DevCluster> cl;
   std::vector<Chunk> chunks;
@@ -251,13 +257,13 @@ struct Counts {
   long long nsymtab = 0, nbands = 0, symdoubles = 0;            // symmetric path (table entries, most bands)
 };
 
-Layout make_layout(const Counts& m) {
+Layout make_layout(const Counts& m, size_t cluster_bytes = sizeof(DevCluster)) {
   const int B = m.B, nchunks = m.nchunks, nstiles = m.nstiles;
   const long long ntot = m.ntot, nitems_max = m.nitems, npart = m.npart, nflagwords = m.nflagwords, ntiles = m.ntiles;
   Layout L{};
   size_t o = 0;
   L.cl = o;
-  o = align_up(o + sizeof(DevCluster) * B);
+  o = align_up(o + cluster_bytes * B);
   L.chunks = o;
   o = align_up(o + sizeof(Chunk) * nchunks);
   L.stiles = o;
@@ -402,7 +408,7 @@ int build_plan(const nbody_system* sys, Plan& p, size_t limit = 0) {
   one.nrecords = p.nchunks;
   one.nstiles = m.nstiles;
   m.nbands = 2 * p.ndelta;
-  const Layout l1 = make_layout(one);
+  const Layout l1 = make_layout(one, kLimitCluster);
   p.onesided = l1.total;
   p.onesided_blob = l1.blob;
   std::stable_sort(p.sym.begin(), p.sym.end(), [&](int x, int y) { return p.cl[x].n > p.cl[y].n; });
@@ -1136,12 +1142,12 @@ int nbody_accel_noalloc(nbody_ctx* ctx, const nbody_system* sys, const double* p
   Plan& p = ctx ? ctx->plan : local;
   int rc = build_plan(sys, p, kScratchBytes);
   if (rc) return rc;
-  if (p.onesided > kScratchBytes)
+  if (p.onesided > NB_NOALLOC_SCRATCH_BYTES)
     return fail(NB_ERR_ARG, "the system needs %zu bytes of workspace; the no-allocation scratch holds %zu",
-                p.onesided, kScratchBytes);
-  if (p.onesided_blob > kScratchTableBytes)
+                p.onesided, NB_NOALLOC_SCRATCH_BYTES);
+  if (p.onesided_blob > NB_NOALLOC_TABLE_BYTES)
     return fail(NB_ERR_ARG, "the system's tables take %zu bytes; the no-allocation staging buffer holds %zu",
-                p.onesided_blob, kScratchTableBytes);
+                p.onesided_blob, NB_NOALLOC_TABLE_BYTES);
   if (p.L.total > kScratchBytes || p.L.blob > kScratchTableBytes)
     return fail(NB_ERR_ARG, "the system does not fit the no-allocation scratch (%zu bytes, tables %zu)", p.L.total,
                 p.L.blob);
