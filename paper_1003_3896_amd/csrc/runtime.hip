@@ -128,6 +128,7 @@ struct Slot {
 #define NB_SPLIT_CAP (1LL << 22)  // bound on N x ranges (partial sums kept per cluster)
 #endif
 constexpr int kMaxSplit = 16;          // ranges of clusters of at least kSplit16 particles
+constexpr int kMaxSplitOneSided = 8;   // of those that the one-sided kernel takes (kSymMin <= kSplit16 <= kSymMax)
 constexpr int kSplit16 = 1 << 15;      // (smaller clusters: at most 8)
 int split_of(int n) {
   const int smax = n >= kSplit16 ? kMaxSplit : 8;
@@ -141,7 +142,12 @@ int split_of(int n) {
 // which leaves 2^18 particles inside the static scratch of the no-allocation entry point) for smaller
 // ones; at least two rows per band, with the potential.  More room means fewer bands, and at the end of
 // each the chip runs empty (N = 983040 with 8 rows: 7% slower than with 33).
+// All clusters of a batch together: kSymRoom bytes above their least room, which is less than their j-ranges
+// would take; the bands are then the shorter in proportion.  100 clusters of 65536 in FP32DL: a workspace of
+// 20.4 GiB and 92.0 ms per leapfrog step without this bound, 3.7 GiB and 97.2 ms with it (one-sided kernel: 3.7
+// GiB, 125 ms); 1500 of them would ask for 307 GiB, more than the GPU has.
 constexpr int kSymRowsMax = 140;
+constexpr size_t kSymRoom = (size_t)2 << 30;
 long long sym_doubles_min(int n) { return 4LL * n * (sym_sums(n) + 2); }
 long long sym_doubles_want(int n, int nseg) {
   const long long most = 3LL * 34 * std::max(n, 1 << 18);
@@ -412,13 +418,15 @@ int build_plan(const nbody_system* sys, Plan& p, size_t limit = 0) {
   p.onesided = l1.total;
   p.onesided_blob = l1.blob;
   std::stable_sort(p.sym.begin(), p.sym.end(), [&](int x, int y) { return p.cl[x].n > p.cl[y].n; });
-  double share = 1.0;  // of each cluster's room above its least
+  size_t room = kSymRoom;
   if (limit) {
     m.symdoubles = least;
     const size_t base = make_layout(m).total + kAlign;
-    const double spare = base < limit ? (double)((limit - base) / sizeof(double)) : 0.0;
-    if ((double)(want - least) > spare) share = spare / (double)(want - least);
+    room = std::min(room, base < limit ? limit - base : 0);
   }
+  const double spare = (double)(room / sizeof(double));
+  // of each cluster's room above its least
+  const double share = (double)(want - least) > spare ? spare / (double)(want - least) : 1.0;
   m.symdoubles = 0;
   for (int b : p.sym) {
     DevCluster& c = p.cl[b];
@@ -1055,17 +1063,21 @@ size_t nbody_workspace_bytes_max(int64_t max_particles, int32_t max_clusters) {
     return 0;
   }
   const long long n = max_particles, B = max_clusters;
-  // sum ceil(n_c/256) <= B + n/256; sum ceil(n_c/64) split_c <= 16 (B + n/64);
-  // partial-sum rows: sum of split_c n_c over the clusters finished by the combine pass <=
-  // min(16 n, B NB_SPLIT_CAP + n) (split_c n_c <= NB_SPLIT_CAP whenever split_c > 1, and an unsplit
-  // cluster there, one in the second galaxy model, adds its n_c)
+  // sum ceil(n_c/256) <= B + n/256; sum ceil(n_c/64) split_c <= 8 (B + n/64), since the one-sided clusters
+  // have at most 8 ranges; partial-sum rows: sum of split_c n_c over the one-sided clusters finished by the
+  // combine pass <= min(8 n, B NB_SPLIT_CAP + n) (split_c n_c <= NB_SPLIT_CAP whenever split_c > 1, and an
+  // unsplit cluster there, one in the second galaxy model, adds its n_c).  Instead of such rows a symmetric
+  // cluster has its least room, at most 6 n_c rows of their size, n_c + 5/4 NB_SPLIT_CAP at most, and shares
+  // kSymRoom: npart bounds both
   Counts m;
   m.B = (int)B;
   m.ntot = n;
   m.nchunks = (int)(B + n / kChunk);
-  m.nrecords = B + 4 * (n / kChunk);  // a cluster with four records per chunk has at least 16 chunks
-  m.nitems = kMaxSplit * (B + n / 64);
-  m.npart = std::min(kMaxSplit * n, B * (long long)NB_SPLIT_CAP + n);
+  // four records per chunk in the clusters of the symmetric path: sum ceil(n_c/256) of them, and 3 more of each
+  const long long bs = std::min(B, n / kSymMin);  // clusters that can be on the symmetric path
+  m.nrecords = B + 3 * bs + 4 * (n / kChunk + 1);
+  m.nitems = kMaxSplitOneSided * (B + n / 64);
+  m.npart = std::min(kMaxSplitOneSided * n, B * (5 * (long long)NB_SPLIT_CAP / 4) + n);
   m.nstiles = (int)(B + n / kSortTile);  // the sort of NB_FP32DL
   // far-tile words: sum over clusters of ceil(n_c/64) split_c ceil(jlen_c/2048)
   // <= (n/64 + B) (16 + (n + 16)/2048), since split_c <= 16 and split_c jlen_c <= n_c + split_c
@@ -1073,14 +1085,13 @@ size_t nbody_workspace_bytes_max(int64_t max_particles, int32_t max_clusters) {
   // j-tile boxes: sum over clusters of split_c ceil(jlen_c/128) <= n/128 + 17 B
   m.ntiles = n / 128 + (kMaxSplit + 1) * B;
   if (n >= kSymMin) {
-    // distances of a cluster: ceil(n_c / seg_c) / 2 + 1 <= n_c/512 + 2; room: at most kSymRowsMax rows of 3
-    // doubles per particle
-    const long long bs = std::min(B, n / kSymMin);  // clusters that can be on the symmetric path
+    // distances of a cluster: ceil(n_c / seg_c) / 2 + 1 <= n_c/512 + 2; room above the least: at most
+    // kSymRowsMax rows of 3 doubles per particle
     m.nbands = 2 * (n / 512 + 2);
     m.nsymtab = n / 512 + 2 * bs;
-    m.symdoubles = 3 * kSymRowsMax * n;
+    m.symdoubles = std::min(3LL * kSymRowsMax * n, (long long)(kSymRoom / sizeof(double)));
   }
-  return make_layout(m).total;
+  return make_layout(m).total + kAlign;  // (the alignment between npart and symdoubles)
 }
 
 int64_t nbody_interactions(const nbody_system* sys) {
