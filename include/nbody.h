@@ -31,22 +31,26 @@
  *   term, as the paper does in Sect. 4.2.
  *
  * Precision modes (nbody_system.prec)
- *   NB_FP32    pure single precision: pairs, accumulation and state updates in FP32; every state
- *              value the library writes is an FP32 value stored in the float64 arrays.
+ *   NB_FP32    pure single precision: pairs, accumulation and state updates in FP32 (clusters of 4096
+ *              to 2^20 particles fold their FP32 sums into FP64); every state value the library writes
+ *              is an FP32 value stored in the float64 arrays.
  *   NB_FP32C   FP32 pair arithmetic on coordinates taken relative to each cluster's centre of
- *              mass (computed in FP64); per-tile FP32 partial sums folded into FP64; FP64 state.
+ *              mass (computed in FP64); FP32 partial sums of a tile's share (32 terms in clusters of
+ *              4096 to 2^20 particles) folded into FP64; FP64 state.
  *   NB_FP32DS  as NB_FP32C, but every coordinate is held as a double-single pair (hi + lo FP32)
  *              and the coordinate difference of each pair is formed from both parts, the
  *              precision-recovery scheme of Sect. 5.2.
  *   NB_FP64    all FP64.
  *   NB_FP32DL  the accuracy of NB_FP32DS at close to the cost of NB_FP32C: each evaluation sorts
- *              every cluster's particles along a Hilbert curve of their FP64 positions; each pair
- *              work item takes coordinates relative to the centre of its own i-particles' bounding
- *              box; a j-tile all of whose sources lie at least 3/4 of the box diagonal from that
- *              centre is computed in FP32 on those local coordinates (coordinate-difference error
- *              at most 1.5 x 2^-22 relative), any other in double-single as NB_FP32DS.  Sums
- *              folded into FP64 per tile as in NB_FP32C.  Clusters of fewer than 4096 particles,
- *              nearly all of whose tiles would be near, are not sorted and run as NB_FP32DS.
+ *              every cluster's particles along a Hilbert curve of their FP64 positions; coordinates are
+ *              taken relative to the centre of a bounding box, of 256 consecutive i-particles (clusters
+ *              above 2^20 particles: of a work item's); sources all of which lie at least 3/4 of the box
+ *              diagonal from that centre, 64 of them at a time (above 2^20: a full j-tile), are computed
+ *              in FP32 on those local coordinates (coordinate-difference error at most 1.5 x 2^-22
+ *              relative), any others in double-single as NB_FP32DS.  Sums folded into FP64 as in
+ *              NB_FP32C, every 16 terms of near sources up to 2^20 particles.  Clusters of fewer than
+ *              4096 particles, nearly all of whose sources would be near, are not sorted and run as
+ *              NB_FP32DS with the launch shapes of this mode.
  *
  * Errors
  *   Every function returns NB_OK (0) or a negative status.  All argument checks run on the host
@@ -122,7 +126,7 @@ typedef struct {
 } nbody_system;
 
 /* Create a context bound to HIP device `device` (>= 0).  The context caches launch plans and
- * tile choices; it owns a small pinned host staging area (NB_NOALLOC_TABLE_BYTES for the
+ * tile choices; it owns a small pinned host staging area (NB_NOALLOC_TABLE_BYTES and 1 MiB for the
  * no-allocation entry point, plus a ring that grows with the tables of the other calls) and never
  * allocates device memory.  It also looks up the device's copy of the static scratch of
  * nbody_accel_noalloc (the first context on a device loads the library's code objects there).
@@ -136,12 +140,11 @@ void nbody_destroy(nbody_ctx* ctx);
  * nbody_last_error() says why): 32 bytes per particle; for clusters of 4096 to 2^20 particles
  * 32 bytes per particle and segment (segments of 256 particles below 8192, 512 below 131072, 1024 from
  * there) but at most 3360 bytes per particle, 204 MiB below 2^18 particles and 816 bytes per particle
- * above; for the others 32
- * bytes per particle and j-range where the sums are split into several source ranges (a cluster of N
- * particles has about 2^22/N ranges, a power of two of at most 8 (16 from 2^15 particles on) with at
- * least 128 sources each; an unsplit cluster in the
- * NB_GALAXY_ALLEN_SANTILLAN field takes one such range too, since a separate pass finishes it);
- * plus 48 bytes per particle, 4 KiB per 2048 particles and 4 KiB per cluster for the sort of
+ * above, and all such clusters together at most 2 GiB above their least, 192 bytes per particle (96 from
+ * 131072 on); for the others 32 bytes per particle and j-range where the sums are split into several
+ * source ranges (a cluster of N particles has about 2^22/N ranges, a power of two of at most 8, with at
+ * least 128 sources each; an unsplit cluster in the NB_GALAXY_ALLEN_SANTILLAN field takes one such range
+ * too, since a separate pass finishes it); plus 48 bytes per particle, 4 KiB per 2048 particles and 4 KiB per cluster for the sort of
  * NB_FP32DL, and for its frames and far-tile bits 32 bytes per 256 particles, or in the split clusters
  * 32 bytes per 64 particles and range plus N_b^2 / 2^15 bytes per cluster, plus O(B + N/64) bookkeeping.  The
  * workspace must be 256-byte aligned;
@@ -163,15 +166,16 @@ int nbody_accel(nbody_ctx* ctx, const nbody_system* sys, const double* pos, cons
 
 /* nbody_accel without a caller workspace, for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid allocation).  The workspace
- * is a static device array of NB_NOALLOC_SCRATCH_BYTES inside the library, one per GPU, held from
- * the library's first use on that GPU until the process ends; the tables go up through a pinned
- * staging buffer of NB_NOALLOC_TABLE_BYTES that nbody_create allocated.  The call itself allocates
+ * is a static device array of NB_NOALLOC_SCRATCH_BYTES and 1 MiB inside the library, one per GPU, held
+ * from the library's first use on that GPU until the process ends; the tables go up through a pinned
+ * staging buffer of NB_NOALLOC_TABLE_BYTES and 1 MiB that nbody_create allocated.  The call itself allocates
  * nothing (no hipMalloc, hipFree or pinned allocation).  Same arguments, results and errors as
  * nbody_accel, and bitwise the same accelerations and potentials (clusters of 4096 to 2^20 particles
  * take fewer segments at a time where the scratch has no room for more).  Limits: a system that with
- * every cluster split into j-ranges would need more than NB_NOALLOC_SCRATCH_BYTES of workspace (a
- * single cluster of more than about 8.1 million particles, 1.4 million in NB_FP32DL) or more than
- * NB_NOALLOC_TABLE_BYTES of tables (more than about 39,000 clusters) returns NB_ERR_ARG; these two
+ * every cluster split into j-ranges (there 16 from 2^15 particles on) would need more than
+ * NB_NOALLOC_SCRATCH_BYTES of workspace (a single cluster of more than about 8.1 million particles, 1.4
+ * million in NB_FP32DL) or more than NB_NOALLOC_TABLE_BYTES of tables (72 bytes per cluster, 16 per 256
+ * particles, per 64 particles and range, and 4: more than 38,836 clusters) returns NB_ERR_ARG; these two
  * checks run first and need neither a context nor a GPU.  Every call on one GPU shares that GPU's scratch, which keeps the
  * last call's contents (the per-call counters are cleared by the call's own table upload): calls
  * that overlap on one GPU (several streams, threads or contexts at once) race and give wrong
@@ -246,16 +250,19 @@ const char* nbody_last_error(void);
  * the others have one fixed shape) for one precision family and cluster-size class:
  *   prec  NB_FP32 / NB_FP32C (share a kernel), NB_FP32DS, NB_FP64 or NB_FP32DL
  *   nclass 0: largest cluster < 2048 particles, 1: < 32768, 2: < 131072, 3: larger
+ *         (of the batch's clusters below 4096 and, separately, above 2^20 particles; class 2 is accepted
+ *         and decides nothing)
  *   k     i-particles per lane; waves_per_group  wavefronts sharing the same i-particles, each
  *         taking 1/waves_per_group of every j-tile; (k, waves_per_group) in {(1,1), (1,2), (1,4),
  *         (2,2), (2,4)}; one work item covers 256 k / waves_per_group particles
  *         (NB_FP32DL: all but (1,1))
  *   tile  j-records per LDS tile (128 or 256); FP32 partial sums are folded into FP64 after every
  *         tile/waves_per_group terms, so tile and waves_per_group change the last bits of FP32-mode
- *         results while k and blocks_per_cu never do (in NB_FP32DL k does too: it sets the work
- *         item whose bounding box the local coordinates are centred on); 1 is taken in place of 2
- *         where a batch has fewer than two items per compute unit
- *   blocks_per_cu  persistent blocks per compute unit (1..8)
+ *         results while k and blocks_per_cu never do (above 2^20 particles in NB_FP32DL k
+ *         does too: it sets the work item whose bounding box the local coordinates are centred on); below
+ *         4096 particles 1 is taken in place of 2 where a batch has fewer than two items per compute unit,
+ *         and in NB_FP64 with the potential where waves_per_group is 2
+ *   blocks_per_cu  persistent blocks per compute unit (1..8), as many as it holds at once
  *   phased  FP32 families only: full tiles are evaluated in groups of 8 pair terms whose
  *         reciprocal square roots issue back to back (shapes (1,4,256), (2,2,256), (2,4,*));
  *         the arithmetic of every term is unchanged
@@ -277,7 +284,8 @@ int nbody_get_tile(const nbody_ctx* ctx, int32_t prec, int32_t nclass, nbody_til
 int nbody_use_graphs(nbody_ctx* ctx, int enable);
 
 /* Per-kernel timing with HIP events recorded on the call's stream around the pair kernels of every
- * evaluation (enable = 1) or off (0, the default).  nbody_timing_read returns the summed duration
+ * evaluation, from the first to the last, with the sums of rows between bands (enable = 1), or off (0,
+ * the default).  nbody_timing_read returns the summed duration
  * in milliseconds and the number of timed evaluations since the last read, waiting for the
  * recorded events to complete; it resets the counters. */
 int nbody_timing_enable(nbody_ctx* ctx, int enable);

@@ -67,9 +67,11 @@ struct PairItem {
 
 // ---- The symmetric path (pair_sym.h) ---------------------------------------------------------
 // Clusters of kSymMin to kSymMax particles.  Below, one cluster alone is too few items to fill the
-// chip (N = 3840 in FP64: 52 us per step one-sided); above, the rows would not fit the static scratch of
-// nbody_accel_noalloc beside what the one-sided path needs there (4 rows of 32 bytes per particle at
-// 2^20 particles against 4 ranges).
+// chip (N = 3840 in FP64: 52 us per step one-sided).  Up to 2^20 a cluster's least room (at most 192 bytes per
+// particle, 96 from 131072 on) is less than its j-ranges would take (256 to 512, 128 at 2^20), so whatever fitted
+// nbody_accel_noalloc with ranges fits with rows.  Above, there are 2 ranges or 1 (64 bytes or none) and that
+// no longer holds by itself: one cluster fits up to about 2 million particles (in NB_FP32DL up to its limit
+// of 1.4), batches near the scratch limit do not.  The path has not been measured there.
 constexpr int kSymMin = 4096, kSymMax = 1 << 20;
 constexpr int kSymBlocksPerCu = 2;  // of 8 waves: 4 per SIMD, an even number (pair_sym.h)
 // Particles per segment, a function of the cluster's size alone (its sums, and so its bits, depend on

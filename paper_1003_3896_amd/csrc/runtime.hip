@@ -127,7 +127,8 @@ struct Slot {
 #ifndef NB_SPLIT_CAP
 #define NB_SPLIT_CAP (1LL << 22)  // bound on N x ranges (partial sums kept per cluster)
 #endif
-constexpr int kMaxSplit = 16;          // ranges of clusters of at least kSplit16 particles
+constexpr int kMaxSplit = 16;          // ranges of clusters of at least kSplit16 particles: since the symmetric
+                                       // path takes them, only in what nbody_accel_noalloc's limits count
 constexpr int kMaxSplitOneSided = 8;   // of those that the one-sided kernel takes (kSymMin <= kSplit16 <= kSymMax)
 constexpr int kSplit16 = 1 << 15;      // (smaller clusters: at most 8)
 int split_of(int n) {
