@@ -261,7 +261,7 @@ const char* nbody_last_error(void);
  *         results while k and blocks_per_cu never do (above 2^20 particles in NB_FP32DL k
  *         does too: it sets the work item whose bounding box the local coordinates are centred on); below
  *         4096 particles 1 is taken in place of 2 where a batch has fewer than two items per compute unit,
- *         and in NB_FP64 with the potential where waves_per_group is 2
+ *         and 4 where it has more than eight of shape (2, 4, 128) in the FP32 and double-single families
  *   blocks_per_cu  persistent blocks per compute unit (1..8), as many as it holds at once
  *   phased  FP32 families only: full tiles are evaluated in groups of 8 pair terms whose
  *         reciprocal square roots issue back to back (shapes (1,4,256), (2,2,256), (2,4,*));

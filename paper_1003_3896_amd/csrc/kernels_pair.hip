@@ -13,6 +13,10 @@ bool tile_supported(int family, const TileCfg& t) {
   return kw && ph && (t.tile == 128 || t.tile == 256) && t.bpc >= 1 && t.bpc <= 8;
 }
 
+bool wide_compiled(int family, const TileCfg& t) {
+  return (family == FAM_F32 || family == FAM_DS) && t.w == 4 && t.tile == 128;
+}
+
 PairFn pair_kernel(int prec, const TileCfg& t, bool mask, bool potmode) {
   if (prec == 4) return pair_kernel_dl(t, true, mask, potmode);
   if (prec == 3) return pair_kernel_f64(t, true, mask, potmode);

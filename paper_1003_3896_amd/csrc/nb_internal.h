@@ -248,6 +248,8 @@ hipError_t launch_sort(const Args& a, int B, hipStream_t s);
 
 
 bool tile_supported(int family, const TileCfg& t);
+// the shape's kernel with four i-particles per lane exists (the runtime's choice only)
+bool wide_compiled(int family, const TileCfg& t);
 // i-particles of one pair work item for a shape
 inline int item_tile(const TileCfg& t) { return 64 * t.k * (4 / t.w); }
 

@@ -217,64 +217,70 @@ __device__ __forceinline__ void store_xfar_tile(PairLds<FAM, T>& sh, const TileR
 }
 
 // Combine the W per-wave FP64 partial sums of every group in LDS (fixed order) and finish.
-// red: [4 waves][64*K lanes][4] doubles (ax, ay, az, pot).
+// red: [4 waves][ax, ay, az, pot][K][64 lanes] doubles.  The waves of a group share its K sums per lane where
+// there are enough of them, else the first takes all.
 template <int K, int W, bool POT>
 __device__ __forceinline__ void reduce_and_finish(const Args& a, const DevCluster& c, const PairItem& item, int ibase,
                                                   const double (&Ax)[K], const double (&Ay)[K], const double (&Az)[K],
                                                   const double (&Pt)[K], double* red, bool round32, int kick) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int sub = wave % W;
+  constexpr bool SHARED = W > 1 && K > 1;
+  static_assert(!SHARED || K % W == 0 || K < W, "the same number of sums for every wave that has any");
+  constexpr int Q = !SHARED ? K : K < W ? 1 : K / W;  // sums of this wave: k = k0, k0 + kstep, ..
+  const int k0 = SHARED ? wave_uniform(sub) : 0;
+  constexpr int kstep = SHARED ? W : 1, S = 64 * K;
   if constexpr (W > 1) {
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      double* r = red + ((size_t)wave * 64 * K + k * 64 + lane) * 4;
+      double* r = red + (wave * 4 * K + k) * 64 + lane;
       r[0] = Ax[k];
-      r[1] = Ay[k];
-      r[2] = Az[k];
-      r[3] = POT ? Pt[k] : 0.0;
+      r[S] = Ay[k];
+      r[2 * S] = Az[k];
+      if (POT) r[3 * S] = Pt[k];
     }
     __syncthreads();
+    if (sub >= (SHARED ? K : 1)) return;
   }
-  double ax[K], ay[K], az[K], pt[K];
+  double ax[Q], ay[Q], az[Q], pt[Q];
 #pragma unroll
-  for (int k = 0; k < K; ++k) {
-    ax[k] = Ax[k];
-    ay[k] = Ay[k];
-    az[k] = Az[k];
-    pt[k] = POT ? Pt[k] : 0.0;
+  for (int q = 0; q < Q; ++q) {
+    const double* r = red + ((wave - sub) * 4 * K + k0 + kstep * q) * 64 + lane;
+    ax[q] = SHARED ? r[0] : Ax[q];
+    ay[q] = SHARED ? r[S] : Ay[q];
+    az[q] = SHARED ? r[2 * S] : Az[q];
+    pt[q] = !POT ? 0.0 : SHARED ? r[3 * S] : Pt[q];
     if constexpr (W > 1) {
-      if (sub != 0) continue;  // only the first wave of a group combines its group's partial sums
 #pragma unroll
       for (int s = 1; s < W; ++s) {
-        const double* r = red + ((size_t)(wave + s) * 64 * K + k * 64 + lane) * 4;
-        ax[k] += r[0];
-        ay[k] += r[1];
-        az[k] += r[2];
-        if (POT) pt[k] += r[3];
+        r += 4 * S;
+        ax[q] += r[0];
+        ay[q] += r[S];
+        az[q] += r[2 * S];
+        if (POT) pt[q] += r[3 * S];
       }
     }
   }
-  if (sub != 0) return;
   if (c.split > 1 || (c.flags & kFlagDefer)) {
     // one j-range of a split cluster (or the only range of a deferred one): the combine pass adds
     // the ranges in range order and finishes the particles (kernel boundaries, not device-scope
     // fences, order the two: a fence inside this persistent kernel would write back and invalidate
     // the XCD's L2)
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const int li = ibase + k * 64;
-      if (li < c.n) a.part[c.part_off + (long long)item.js * c.n + li] = make_double4(ax[k], ay[k], az[k], pt[k]);
+    for (int q = 0; q < Q; ++q) {
+      const int li = ibase + (k0 + kstep * q) * 64;
+      if (li < c.n) a.part[c.part_off + (long long)item.js * c.n + li] = make_double4(ax[q], ay[q], az[q], pt[q]);
     }
     return;
   }
 #pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const int li = ibase + k * 64;
+  for (int q = 0; q < Q; ++q) {
+    const int li = ibase + (k0 + kstep * q) * 64;
     if (li >= c.n) continue;
     const long long gi = particle_index(a, c, li);
-    finish_particle<false>(a, c, item.cluster, gi, ax[k], ay[k], az[k], round32, kick);
-    if (POT && a.pot) a.pot[gi] = round32 ? (double)(-(float)a.G * (float)pt[k]) : -a.G * pt[k];
+    finish_particle<false>(a, c, item.cluster, gi, ax[q], ay[q], az[q], round32, kick);
+    if (POT && a.pot) a.pot[gi] = round32 ? (double)(-(float)a.G * (float)pt[q]) : -a.G * pt[q];
   }
 }
 
@@ -652,6 +658,12 @@ __global__ __launch_bounds__(kBlock) void k_pair32(Args a, int kick) {
   pair32_items<FAM, K, W, T, FOLD, MASK, POT, PH>(a, kick);
 }
 
+// Four i-particles per lane, held to 4 waves per SIMD (128 VGPRs; an even number of waves, pair_sym.h).
+template <int FAM, int W, int T, bool FOLD, bool MASK, bool POT>
+__global__ __launch_bounds__(kBlock, 4) void k_pair32_wide(Args a, int kick) {
+  pair32_items<FAM, 4, W, T, FOLD, MASK, POT, false>(a, kick);
+}
+
 // The local family is built for 6 waves per SIMD (at most 80 VGPRs): with both loops in one kernel
 // the compiler would otherwise settle on 3, and the extra waves hide more of the FP32 chain's
 // latency.  The price is a few dozen work-item set-up values spilled to scratch and reloaded once
@@ -754,6 +766,12 @@ __global__ __launch_bounds__(kBlock) void k_pair64(Args a, int kick) {
 }
 
 // Kernel for one shape and flag set of a family (nullptr when not compiled in).
+template <int FAM, int W, int T, bool FOLD>
+PairFn pair_wide(bool mask, bool pot) {
+  if (mask) return pot ? k_pair32_wide<FAM, W, T, FOLD, true, true> : k_pair32_wide<FAM, W, T, FOLD, true, false>;
+  return pot ? k_pair32_wide<FAM, W, T, FOLD, false, true> : k_pair32_wide<FAM, W, T, FOLD, false, false>;
+}
+
 template <int FAM, int K, int W, int T>
 PairFn pair_flags(bool fold, bool mask, bool pot) {
   if constexpr (FAM == FAM_F64) {
@@ -777,7 +795,8 @@ PairFn pair_flags(bool fold, bool mask, bool pot) {
 
 // Compiled-in shapes: (K, W) in {(1,1), (1,2), (1,4), (2,2), (2,4)} (all but (1,1) for the local
 // family), T in {128, 256}; the rsq-phased full-tile loop for the FP32 and double-single
-// families' main shapes, used for folded sums without the self mask or the potential.
+// families' main shapes, used for folded sums without the self mask or the potential; and (4, 4) with T = 128
+// for the batches of many small clusters (wide_compiled).
 template <int FAM>
 PairFn pair_select(const TileCfg& t, bool fold, bool mask, bool pot) {
   if constexpr (FAM == FAM_F32 || FAM == FAM_DS) {
@@ -806,6 +825,9 @@ PairFn pair_select(const TileCfg& t, bool fold, bool mask, bool pot) {
   NB_SHAPE(2, 4, 128)
   NB_SHAPE(2, 4, 256)
 #undef NB_SHAPE
+  if constexpr (FAM == FAM_F32 || FAM == FAM_DS)
+    if (t.k == 4 && t.w == 4 && t.tile == 128)
+      return fold || FAM == FAM_DS ? pair_wide<FAM, 4, 128, true>(mask, pot) : pair_wide<FAM, 4, 128, false>(mask, pot);
   return nullptr;
 }
 

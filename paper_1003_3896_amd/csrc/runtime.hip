@@ -571,15 +571,19 @@ int prepare(nbody_ctx* ctx, const nbody_system* sys, void* ws, size_t ws_bytes, 
   lg.nitems = sm.first = (int)items.size();
   sm.prec = sys->prec == NB_FP32DL ? NB_FP32DS : sys->prec;
   sm.tile = ctx->tiles[family_of(sys->prec)][size_class(p.maxn_small)];
-  // one i-particle per lane in place of two (it does not change a result): in FP64 with the potential where
-  // two waves share a group (256 clusters of 2048..4095: 1795 -> 1756 us; with four, 1809 -> 1868, and without
-  // the potential two are faster, 1501 to 1550), and where there are fewer than two items per CU, halves of
-  // which fill the chip better
-  if (sm.prec == NB_FP64 && pot && sm.tile.k == 2 && sm.tile.w == 2) sm.tile.k = 1;
+  // The i-particles per lane do not change a result, so they follow the number of items: one in place of two where
+  // there are fewer than two items per CU, halves of which fill the chip better, and four where four waves share
+  // a group and there are more than 8 items per CU (a leapfrog step of 1000 clusters of 256..2047 in FP32 617 ->
+  // 432 us, FP32C 618 -> 445, FP32DS 603 -> 559, 64 of them 63 -> 54.6, 62 -> 54.6 and 65 -> 61; but 32 in FP32DS 42.6
+  // -> 46.4)
   if (p.maxn_small) {
     make_items(p, sm.tile, items, true, false);
-    if ((int)items.size() - sm.first < 2 * ctx->cus && sm.tile.k == 2) {
+    const int n = (int)items.size() - sm.first, k = sm.tile.k;
+    if (k == 2 && n < 2 * ctx->cus)
       sm.tile.k = 1;
+    else if (k == 2 && n > 8 * ctx->cus && wide_compiled(family_of(sm.prec), sm.tile))
+      sm.tile.k = 4;
+    if (sm.tile.k != k) {
       sm.tile.phase = 0;
       items.resize(sm.first);
       make_items(p, sm.tile, items, true, false);
