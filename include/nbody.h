@@ -126,7 +126,7 @@ typedef struct {
 } nbody_system;
 
 /* Create a context bound to HIP device `device` (>= 0).  The context caches launch plans and
- * tile choices; it owns a small pinned host staging area (NB_NOALLOC_TABLE_BYTES and 1 MiB for the
+ * tile choices; it owns a small pinned host staging area (NB_NOALLOC_TABLE_BYTES for the
  * no-allocation entry point, plus a ring that grows with the tables of the other calls) and never
  * allocates device memory.  It also looks up the device's copy of the static scratch of
  * nbody_accel_noalloc (the first context on a device loads the library's code objects there).
@@ -166,9 +166,9 @@ int nbody_accel(nbody_ctx* ctx, const nbody_system* sys, const double* pos, cons
 
 /* nbody_accel without a caller workspace, for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid allocation).  The workspace
- * is a static device array of NB_NOALLOC_SCRATCH_BYTES and 1 MiB inside the library, one per GPU, held
+ * is a static device array of NB_NOALLOC_SCRATCH_BYTES inside the library, one per GPU, held
  * from the library's first use on that GPU until the process ends; the tables go up through a pinned
- * staging buffer of NB_NOALLOC_TABLE_BYTES and 1 MiB that nbody_create allocated.  The call itself allocates
+ * staging buffer of NB_NOALLOC_TABLE_BYTES that nbody_create allocated.  The call itself allocates
  * nothing (no hipMalloc, hipFree or pinned allocation).  Same arguments, results and errors as
  * nbody_accel, and bitwise the same accelerations and potentials (clusters of 4096 to 2^20 particles
  * take fewer segments at a time where the scratch has no room for more).  Limits: a system that with

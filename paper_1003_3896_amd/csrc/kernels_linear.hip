@@ -227,7 +227,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce(Args a) {
   const int t = threadIdx.x;
   double tot[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
   double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (int q = t; q < c.nchunks; q += kBlock) {
+  for (int q = t; q < chunks_of(c); q += kBlock) {
     for (int r = 0; r < 5; ++r) tot[r] += chunk_sum(a, c, q, r);
     const double* p = partial_record(a, c, q, 0);
     if (c.nstiles)
@@ -299,11 +299,11 @@ __global__ __launch_bounds__(kBlock) void k_energy(Args a) {
 #pragma unroll
     for (int k = 0; k < NS; ++k) a.epart[(size_t)blockIdx.x * NS + k] = q[k];
   }
-  if (!last_block_of_cluster(&a.chunk_counter[ch.cluster], c.nchunks)) return;
+  if (!last_block_of_cluster(&a.chunk_counter[ch.cluster], chunks_of(c))) return;
   double tot[NS];
 #pragma unroll
   for (int k = 0; k < NS; ++k) tot[k] = 0.0;
-  for (int p = t; p < c.nchunks; p += kBlock) {
+  for (int p = t; p < chunks_of(c); p += kBlock) {
     const double* e = a.epart + (size_t)(c.chunk0 + p) * NS;
 #pragma unroll
     for (int k = 0; k < NS; ++k) tot[k] += e[k];

@@ -205,7 +205,7 @@ __device__ __forceinline__ double chunk_sum(const Args& a, const DevCluster& c, 
 template <bool CENTRE>
 __device__ __forceinline__ double4 chunk_frame(const Args& a, const DevCluster& c, double& mc) {
   const int lane = threadIdx.x & 63;
-  const bool has = lane < c.nchunks;
+  const bool has = lane < chunks_of(c);
   const double* p = partial_record(a, c, has ? lane : 0, 0);
   mc = __any(has && p[4] != 0.0) ? 0.0 : a.mass[c.off];
   if (!CENTRE) return make_double4(0.0, 0.0, 0.0, 0.0);

@@ -21,7 +21,8 @@ constexpr int kSortTile = 2048;
 constexpr int kRadixBits = 10;
 constexpr int kRadix = 1 << kRadixBits;
 
-// Per-cluster descriptor in device memory (uploaded with every call).
+// Per-cluster descriptor in device memory (uploaded with every call).  72 bytes: the table limit of
+// nbody_accel_noalloc counts them.
 struct DevCluster {
   long long off;       // first particle of the cluster in the concatenated arrays
   long long part_off;  // first row of the cluster's partial sums ([split][n] rows), when split > 1
@@ -31,18 +32,23 @@ struct DevCluster {
   double eps2;         // eps^2 in FP64
   float eps2f;         // eps^2 rounded to FP32
   int chunk0;          // first O(N) chunk of the cluster
-  int nchunks;         // O(N) chunks of the cluster
-  int split;           // the j-sum of every particle is split into this many ranges (1 = none)
-  int jlen;            // sources per range (the last range may be shorter)
+  union {
+    struct {           // one-sided path
+      int split;       // the j-sum of every particle is split into this many ranges (1 = none)
+      int jlen;        // sources per range (the last range may be shorter)
+    };
+    long long sym_doubles;  // symmetric path: room for its rows (doubles)
+  };
   int stile0;          // first sort tile of the cluster (NB_FP32DL)
   int nstiles;         // sort tiles of the cluster
   int tbox0;           // first j-tile box of the cluster (NB_FP32DL; room for split x ceil(jlen/128))
   int seg;             // symmetric path: particles per segment (0: the cluster takes the one-sided path)
   int nseg;            // symmetric path: segments
   int rec0;            // first partial record of the cluster (chunk_records per chunk)
-  int pad0;
-  long long sym_doubles;  // symmetric path: room for its rows (doubles)
 };
+static_assert(sizeof(DevCluster) == 72, "the uploaded tables' layout");
+// O(N) chunks of a cluster
+__host__ __device__ inline int chunks_of(const DevCluster& c) { return (c.n + kChunk - 1) / kChunk; }
 constexpr int kFlagField = 1;     // add the galaxy field
 constexpr int kFlagMaskSelf = 2;  // eps == 0: the j = i term must be excluded explicitly
 constexpr int kFlagDefer = 4;     // finished by the combine pass even when unsplit (its galaxy model

@@ -111,7 +111,6 @@ __device__ __forceinline__ DevCluster uniform_cluster(const Args& a, int b) {
   u.eps2 = wave_uniform(c.eps2);
   u.eps2f = wave_uniform(c.eps2f);
   u.chunk0 = wave_uniform(c.chunk0);
-  u.nchunks = wave_uniform(c.nchunks);
   u.split = wave_uniform(c.split);
   u.jlen = wave_uniform(c.jlen);
   u.stile0 = wave_uniform(c.stile0);

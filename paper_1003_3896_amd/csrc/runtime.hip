@@ -69,13 +69,9 @@ const Sym6 kSym6;
 // name is a stand-in, not a device address): the address of each device's copy is looked up once
 // per device with hipGetSymbolAddress and kept in g_scratch.
 // The limits NB_NOALLOC_SCRATCH_BYTES and NB_NOALLOC_TABLE_BYTES are stated for the layout in which every cluster
-// is split into j-ranges and described by kLimitCluster bytes.  What is uploaded and used beyond that is the
-// rest of its descriptor, at most 621 KB for the 38,836 clusters that the table limit lets through, and a
-// counter per band: it has the room of kBeyondLimit.
-constexpr size_t kLimitCluster = 72, kBeyondLimit = 1 << 20;
-constexpr size_t kScratchBytes = NB_NOALLOC_SCRATCH_BYTES + kBeyondLimit;
-constexpr size_t kScratchTableBytes = NB_NOALLOC_TABLE_BYTES + kBeyondLimit;  // pinned staging of its tables
-static_assert(sizeof(DevCluster) <= kLimitCluster + 16, "kBeyondLimit");
+// is split into j-ranges; symmetric clusters need less than that, of tables too, whatever their bands.
+constexpr size_t kScratchBytes = NB_NOALLOC_SCRATCH_BYTES;
+constexpr size_t kScratchTableBytes = NB_NOALLOC_TABLE_BYTES;  // pinned staging of its tables
 constexpr int kMaxDevices = 64;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 std::mutex g_scratch_mu;
@@ -101,7 +97,7 @@ struct Plan {
   int maxn_small = 0, maxn_large = 0;  // largest one-sided cluster below and above the symmetric path
   std::vector<int> sym;   // clusters on the symmetric path, largest first
   int ndelta = 0;         // segment distances of the largest of them (bounds its bands)
-  size_t onesided = 0;    // workspace bytes if every cluster took the one-sided path (kLimitCluster)
+  size_t onesided = 0;    // workspace bytes if every cluster took the one-sided path
   size_t onesided_blob = 0;
   std::vector<DevCluster> cl;
   std::vector<Chunk> chunks;
@@ -264,13 +260,13 @@ struct Counts {
   long long nsymtab = 0, nbands = 0, symdoubles = 0;            // symmetric path (table entries, most bands)
 };
 
-Layout make_layout(const Counts& m, size_t cluster_bytes = sizeof(DevCluster)) {
+Layout make_layout(const Counts& m) {
   const int B = m.B, nchunks = m.nchunks, nstiles = m.nstiles;
   const long long ntot = m.ntot, nitems_max = m.nitems, npart = m.npart, nflagwords = m.nflagwords, ntiles = m.ntiles;
   Layout L{};
   size_t o = 0;
   L.cl = o;
-  o = align_up(o + cluster_bytes * B);
+  o = align_up(o + sizeof(DevCluster) * B);
   L.chunks = o;
   o = align_up(o + sizeof(Chunk) * nchunks);
   L.stiles = o;
@@ -357,7 +353,6 @@ int build_plan(const nbody_system* sys, Plan& p, size_t limit = 0) {
     if (mask) c.flags |= kFlagMaskSelf;
     p.anymask |= mask;
     c.chunk0 = (int)p.chunks.size();
-    c.nchunks = (c.n + kChunk - 1) / kChunk;
     for (int s = 0; s < c.n; s += kChunk) p.chunks.push_back(Chunk{b, s, std::min(kChunk, c.n - s), 0});
     c.split = split_of(c.n);
     c.jlen = (c.n + c.split - 1) / c.split;
@@ -371,13 +366,12 @@ int build_plan(const nbody_system* sys, Plan& p, size_t limit = 0) {
     one.nflagwords += words;
     one.ntiles += boxes;
     c.seg = c.nseg = 0;
-    c.sym_doubles = 0;
     c.part_off = via_combine ? m.npart : 0;
     c.tbox0 = (int)m.ntiles;
     if (c.n >= kSymMin && c.n <= kSymMax) {
       c.seg = sym_segment(c.n);
       c.nseg = (c.n + c.seg - 1) / c.seg;
-      c.sym_doubles = sym_doubles_want(c.n, c.nseg);
+      c.sym_doubles = sym_doubles_want(c.n, c.nseg);  // in the place of split and jlen
       want += c.sym_doubles;
       least += sym_doubles_min(c.n);
       p.sym.push_back(b);
@@ -394,7 +388,7 @@ int build_plan(const nbody_system* sys, Plan& p, size_t limit = 0) {
     p.reduce |= !small_cluster(c);
     p.nsmall += small_cluster(c);
     c.rec0 = (int)m.nrecords;
-    m.nrecords += (long long)c.nchunks * chunk_records(c.n, c.seg);
+    m.nrecords += (long long)chunks_of(c) * chunk_records(c.n, c.seg);
     if (sorted) m.nstiles += (c.n + kSortTile - 1) / kSortTile;
     c.stile0 = (int)p.stiles.size();
     c.nstiles = 0;
@@ -415,7 +409,7 @@ int build_plan(const nbody_system* sys, Plan& p, size_t limit = 0) {
   one.nrecords = p.nchunks;
   one.nstiles = m.nstiles;
   m.nbands = 2 * p.ndelta;
-  const Layout l1 = make_layout(one, kLimitCluster);
+  const Layout l1 = make_layout(one);
   p.onesided = l1.total;
   p.onesided_blob = l1.blob;
   std::stable_sort(p.sym.begin(), p.sym.end(), [&](int x, int y) { return p.cl[x].n > p.cl[y].n; });
@@ -1158,12 +1152,12 @@ int nbody_accel_noalloc(nbody_ctx* ctx, const nbody_system* sys, const double* p
   Plan& p = ctx ? ctx->plan : local;
   int rc = build_plan(sys, p, kScratchBytes);
   if (rc) return rc;
-  if (p.onesided > NB_NOALLOC_SCRATCH_BYTES)
+  if (p.onesided > kScratchBytes)
     return fail(NB_ERR_ARG, "the system needs %zu bytes of workspace; the no-allocation scratch holds %zu",
-                p.onesided, NB_NOALLOC_SCRATCH_BYTES);
-  if (p.onesided_blob > NB_NOALLOC_TABLE_BYTES)
+                p.onesided, kScratchBytes);
+  if (p.onesided_blob > kScratchTableBytes)
     return fail(NB_ERR_ARG, "the system's tables take %zu bytes; the no-allocation staging buffer holds %zu",
-                p.onesided_blob, NB_NOALLOC_TABLE_BYTES);
+                p.onesided_blob, kScratchTableBytes);
   if (p.L.total > kScratchBytes || p.L.blob > kScratchTableBytes)
     return fail(NB_ERR_ARG, "the system does not fit the no-allocation scratch (%zu bytes, tables %zu)", p.L.total,
                 p.L.blob);
