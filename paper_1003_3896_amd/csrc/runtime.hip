@@ -179,7 +179,6 @@ struct nbody_ctx {
   hipStream_t gstream = nullptr;  // non-blocking stream the step graphs are captured on
   std::vector<StepGraph> gcache;  // small LRU cache of captured graphs (most recent last)
   TileCfg tiles[kFamilies][kSizeClasses];
-  std::vector<std::pair<PairFn, int>> resident;  // resident_blocks
   Slot slots[4];
   int next_slot = 0;
   bool timing = false;
@@ -667,15 +666,19 @@ hipEvent_t pool_event(nbody_ctx* ctx) {
   return e;
 }
 
-// Blocks of a one-sided pair kernel that a CU holds at once.
-int resident_blocks(nbody_ctx* ctx, PairFn fn) {
-  for (const auto& r : ctx->resident)
+// Blocks of a one-sided pair kernel that a CU holds at once, asked of the runtime once per kernel and process
+// (about 60 us).
+int resident_blocks(PairFn fn) {
+  static std::mutex mu;
+  static std::vector<std::pair<PairFn, int>> known;
+  std::lock_guard<std::mutex> lock(mu);
+  for (const auto& r : known)
     if (r.first == fn) return r.second;
   int n = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void*>(fn), kBlock, 0) != hipSuccess ||
       n < 1)
     n = 1;
-  ctx->resident.emplace_back(fn, n);
+  known.emplace_back(fn, n);
   return n;
 }
 
@@ -693,7 +696,8 @@ int pair_launch(nbody_ctx* ctx, const Prepared& P, const OneSided& o, int counte
   }
   const PairFn fn = pair_kernel(a.prec, o.tile, ctx->plan.anymask, potmode);
   if (!fn) return fail(NB_ERR_HIP, "pair kernel launch: shape not compiled in");
-  const int bpc = std::min(o.tile.bpc, resident_blocks(ctx, fn));
+  // two fit in any case (256 registers); only more items than that need the kernel's own number
+  const int bpc = std::min(o.tile.bpc, o.nitems <= 2 * ctx->cus ? 2 : resident_blocks(fn));
   const hipError_t e = launch_pair(fn, a, std::min(o.nitems, ctx->cus * bpc), kick, s);
   if (e != hipSuccess) return fail(NB_ERR_HIP, "pair kernel launch: %s", hipGetErrorString(e));
   return NB_OK;
