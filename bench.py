@@ -47,8 +47,8 @@ PEAK_FP64_TFLOPS = 78.6
 # VALU instructions per unordered pair of the fastest loop that a workload runs, without these two,
 # counted in the compiled code.
 CYCLES_PER_VALU, CYCLES_PER_RSQ, CYCLES_PER_DPP, DPP_PER_PAIR = 2.07, 8.1, 4.2, 45 / 64
-LOOP_VALU = {("fp32dl", True): 14.72, ("fp32dl", False): 16.72, ("fp32ds", True): 20.75,
-             ("fp32ds", False): 22.75}
+LOOP_VALU = {("fp32dl", True): 14.72, ("fp32dl", False): 17.72, ("fp32ds", True): 20.75,
+             ("fp32ds", False): 23.75}
 METRIC = "G pair-interactions/s & %FP32 VALU peak; batched p50/p99 job latency"
 
 
