@@ -26,7 +26,7 @@ def test_tuned_workloads_run_the_one_sided_kernel_alone():
         assert {autotune.size_class(int(n)) for n in (sizes.min(), sizes.max())} == {ncl}
 
 
-@pytest.mark.parametrize("sizes", [(4096,), (1 << 20,), (300, 65536)])
+@pytest.mark.parametrize("sizes", [(4096,), (1 << 20,), (5000, 65536)])
 def test_sweep_refuses_what_the_shapes_do_not_decide(sizes):
     b = inputs.concat([inputs.single(np.zeros((n, 3)), np.zeros((n, 3)), np.ones(n), 1e-3, False) for n in sizes])
     with pytest.raises(ValueError, match="launch shapes"):
