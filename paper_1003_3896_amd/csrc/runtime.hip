@@ -675,11 +675,12 @@ int resident_blocks(PairFn fn) {
   for (const auto& r : known)
     if (r.first == fn) return r.second;
   int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void*>(fn), kBlock, 0) != hipSuccess ||
-      n < 1)
-    n = 1;
-  known.emplace_back(fn, n);
-  return n;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void*>(fn), kBlock, 0) != hipSuccess) {
+    (void)hipGetLastError();  // not the launch's
+    return 2;
+  }
+  known.emplace_back(fn, std::max(n, 1));
+  return known.back().second;
 }
 
 int pair_launch(nbody_ctx* ctx, const Prepared& P, const OneSided& o, int counter, bool potmode, bool kick,
